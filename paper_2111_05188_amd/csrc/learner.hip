@@ -8,17 +8,16 @@
 //   forward   Z = X W^T                      (A = activations, B = weights)
 //   backward  dH = dZ W   = dZ (W^T)^T       (B = a transposed weight copy)
 //   weights   dW = dZ^T X = (dZ^T)(X^T)^T    (both transposed activations)
-// so the epilogues that produce activations also write their transposes
-// (the MFMA result layout gives each lane four consecutive rows of one
-// column, one 8-byte store).  Actor and critic take the same minibatch
+// so the epilogues that produce activations also write their transposes.
+// Actor and critic take the same minibatch
 // rows, so their first layers run as one product over the concatenated
 // weights [W1; Wc1]; the other products of a stage are grouped into one
 // launch.  bf16 configs use bf16 operands (weights rounded from the fp32
 // masters, observations as stored, hidden activations and backpropagated
 // pre-activation gradients rounded to bf16) with fp32 MFMA accumulation;
-// fp32 configs use an LDS-tiled fp32 kernel.  Bias, log-std and critic-head
+// fp32 configs use fp32 operands and the fp32 MFMA.  Bias, log-std and critic-head
 // gradients are row sums of the transposed gradient blocks (one wave per
-// row, fixed order).  Adam runs over 32x32 tiles of each weight matrix and
+// row, fixed order).  Adam runs over 64x64 tiles of each weight matrix and
 // rewrites the operand copies (and their transposes, through LDS) in the
 // same pass.
 #include <type_traits>
@@ -135,68 +134,14 @@ __device__ __forceinline__ GemmProb agent_prob(const GemmBatch &gb, int pi, int 
 
 constexpr int GT = 64;   // workgroup tile (rows and columns)
 
-template <bool BF>
-__device__ __forceinline__ void epi4(const GemmProb &P, int row0, int col, const float v[4])
+// EPI_BIAS: four rows of one column from the accumulators
+__device__ __forceinline__ void bias4(const GemmProb &P, int row0, int col, const floatx4 &v)
 {
     if (col >= P.N) return;
-    const int mode = P.mode;
-    if (mode == EPI_GRAD) {
-        if (col >= P.gcols) return;
+    const float b = col < P.bsplit ? P.bias0[col] : P.bias1[col - P.bsplit];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = row0 + i;
-            if (r >= P.M) break;
-            float *d = r < P.gsplit ? P.g0 + (size_t)r * P.ldg : P.g1 + (size_t)(r - P.gsplit) * P.ldg;
-            d[col] = v[i];
-        }
-        return;
-    }
-    if (mode == EPI_BIAS) {
-        const float b = col < P.bsplit ? P.bias0[col] : P.bias1[col - P.bsplit];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = row0 + i;
-            if (r >= P.M) break;
-            ((float *)P.out)[(size_t)r * P.ldo + col] = v[i] + b;
-        }
-        return;
-    }
-    Elem<BF> h[4];
-    if (mode == EPI_TANH) {
-        const float b = col < P.bsplit ? P.bias0[col] : P.bias1[col - P.bsplit];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) h[i] = to_elem<BF>(fast_tanh(v[i] + b));
-    } else {   // EPI_DTANH
-        const Elem<BF> *hs = (const Elem<BF> *)P.hsrc;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = min(row0 + i, P.M - 1);
-            const float y = (float)hs[(size_t)col * P.ldh + r];
-            h[i] = to_elem<BF>(v[i] * (1.0f - y * y));
-        }
-    }
-    if (P.out) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int r = row0 + i;
-            if (r >= P.M) break;
-            ((Elem<BF> *)P.out)[(size_t)r * P.ldo + col] = h[i];
-        }
-    }
-    if (P.outT) {
-        Elem<BF> *t = (Elem<BF> *)P.outT + (size_t)col * P.ldt + row0;
-        if (row0 + 3 < P.M) {
-            if constexpr (BF) {
-                *(bf16x4 *)t = bf16x4{h[0], h[1], h[2], h[3]};
-            } else {
-                *(floatx4 *)t = floatx4{h[0], h[1], h[2], h[3]};
-            }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (row0 + i < P.M) t[i] = h[i];
-        }
-    }
+    for (int i = 0; i < 4; ++i)
+        if (row0 + i < P.M) ((float *)P.out)[(size_t)(row0 + i) * P.ldo + col] = v[i] + b;
 }
 
 __device__ __forceinline__ int find_prob(const GemmBatch &g, int t)
@@ -207,15 +152,6 @@ __device__ __forceinline__ int find_prob(const GemmBatch &g, int t)
         if (q < g.np && t >= g.p[q].tile0) pi = q;
     return pi;
 }
-
-// bf16: four waves, each a 32x32 block of the 64x64 tile (2x2 MFMA tiles of
-// 16x16, v_mfma_f32_16x16x32_bf16), fragments loaded straight from global
-// memory (operands are small and L2-resident) through a ring of GEMM_PF
-// k-steps of registers: consuming k-step k issues the loads of k + GEMM_PF,
-// so that many k-steps are in flight to cover the L2 latency.
-#ifndef GEMM_PF
-#define GEMM_PF 8
-#endif
 
 template <int I>
 using ic = std::integral_constant<int, I>;
@@ -229,82 +165,35 @@ __device__ __forceinline__ void static_for(Fn &&fn)
     }
 }
 
-__device__ __forceinline__ void mma_2x2(const bf16x8 a[2], const bf16x8 b[2], floatx4 acc[2][2])
-{
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
-}
+// Products split over the waves of a workgroup (fp32, and bf16 where K is
+// none of the staged kernels'): a tile of 16 F x 16 F, the NW waves taking
+// k-blocks w, w + NW, ... of it (64 bytes of every row: 16 fp32 or 32 bf16),
+// each with F x F accumulators of 16 x 16.  Loads are 16 bytes a lane, four
+// consecutive lanes on 64 contiguous bytes of a row, D blocks ahead in
+// registers; they reach the MFMA's lanes (row r16, piece kq) through LDS of
+// the wave's own.  fp32 operands go to v_mfma_f32_16x16x4_f32: lane (r16,
+// kq) holds k = 4 kq .. 4 kq + 3 of a block, and MFMA e takes element e of
+// every lane.  The waves' partial tiles meet in LDS and are summed in wave
+// order, so results are deterministic.
+// What bounds it at one learner (batch 1,024, 301-256-256-30): launches and
+// one trip to L2 after another; the MFMAs are a fifth of it (a timing copy
+// without them is no faster).  An update of that learner took 273 us with
+// the 64 x 64 VALU kernel this replaced (42 us a product), 94 with fragments
+// loaded straight into the MFMA's lanes (16 rows for 16 consecutive lanes:
+// 11-16 us a product), 75 so (8-12 us).  Measured equal or slower: 3, 6 or 8
+// blocks in flight, 8 or 16 waves (16 waves 24% slower).
+constexpr int ST = 32;        // tile edge
+constexpr int SWAVES = 4;     // waves per workgroup
+constexpr int SD = 4;         // k-blocks in flight per wave
 
-// NK k-steps fully unrolled: every ring slot is a compile-time register
-// set, so each wait is for exactly the k-step about to be used.
-template <int NK, int PF>
-__device__ __forceinline__ void kloop_fixed(const __bf16 *const pa[2], const __bf16 *const pb[2],
-                                            floatx4 acc[2][2])
+template <bool BF, int F, int NW, int D>
+__global__ __launch_bounds__(NW *WAVE) void gemm_split_kernel(GemmBatch gb)
 {
-    constexpr int D = NK < PF ? NK : PF;
-    bf16x8 ra[D][2], rb[D][2];
-    static_for<0, D>([&](auto q) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            ra[q][i] = *(const bf16x8 *)(pa[i] + q * 32);
-            rb[q][i] = *(const bf16x8 *)(pb[i] + q * 32);
-        }
-    });
-    // the scheduling barriers keep each refill where it is issued (the
-    // scheduler would otherwise sink the loads next to their use and
-    // shrink the ring to a step or two)
-    __builtin_amdgcn_sched_barrier(0);
-    static_for<0, NK>([&](auto k) {
-        constexpr int slot = k % D;
-        mma_2x2(ra[slot], rb[slot], acc);
-        if constexpr (k + D < NK) {
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                ra[slot][i] = *(const bf16x8 *)(pa[i] + (k + D) * 32);
-                rb[slot][i] = *(const bf16x8 *)(pb[i] + (k + D) * 32);
-            }
-        }
-        __builtin_amdgcn_sched_barrier(0);
-    });
-}
-
-// Any k-step count: the same ring under a runtime bound.
-template <int PF>
-__device__ __forceinline__ void kloop_any(const __bf16 *const pa[2], const __bf16 *const pb[2],
-                                          floatx4 acc[2][2], int nk)
-{
-    bf16x8 ra[PF][2], rb[PF][2];
-    static_for<0, PF>([&](auto q) {
-        if (q < nk) {
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                ra[q][i] = *(const bf16x8 *)(pa[i] + q * 32);
-                rb[q][i] = *(const bf16x8 *)(pb[i] + q * 32);
-            }
-        }
-    });
-    for (int kb = 0; kb < nk; kb += PF) {
-        static_for<0, PF>([&](auto q) {
-            const int k = kb + q;
-            if (k < nk) {
-                mma_2x2(ra[q], rb[q], acc);
-                if (k + PF < nk) {
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        ra[q][i] = *(const bf16x8 *)(pa[i] + (k + PF) * 32);
-                        rb[q][i] = *(const bf16x8 *)(pb[i] + (k + PF) * 32);
-                    }
-                }
-            }
-        });
-    }
-}
-__global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmBatch gb)
-{
-    constexpr int PF = GEMM_PF;
+    typedef Elem<BF> E;
+    typedef E frag __attribute__((ext_vector_type(16 / sizeof(E))));
+    constexpr int T = 16 * F, KB = 64 / (int)sizeof(E), NT = NW * WAVE;
+    constexpr int PITCH = T + 1;
+    __shared__ __attribute__((aligned(16))) float red[NW][T][PITCH];
     int agent, t;
     if (!gemm_slot(gb, agent, t)) return;
     const int pi = find_prob(gb, t);
@@ -312,35 +201,172 @@ __global__ __launch_bounds__(256) void gemm_bf16_kernel(GemmBatch gb)
     t -= P.tile0;
     const int tn = __builtin_amdgcn_readfirstlane(t % P.tiles_n);
     const int tm = __builtin_amdgcn_readfirstlane(t / P.tiles_n);
-    const int wave = threadIdx.x / WAVE, lane = threadIdx.x % WAVE;
-    const int m0 = tm * GT + (wave >> 1) * 32, n0 = tn * GT + (wave & 1) * 32;
+    const int tid = threadIdx.x, lane = tid % WAVE;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    const int m0 = tm * T, n0 = tn * T;
     const int r16 = lane & 15, kq = lane >> 4;
-    const __bf16 *A = (const __bf16 *)P.A, *B = (const __bf16 *)P.B;
-    const __bf16 *pa[2], *pb[2];
+    // this wave's k-blocks: wave, wave + NW, ... (cnt of them)
+    const int nkb = P.K / KB, cnt = (nkb - wave + NW - 1) / NW;
+    floatx4 acc[F][F];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        pa[i] = A + (size_t)min(m0 + i * 16 + r16, P.M - 1) * P.lda + kq * 8;
-        pb[i] = B + (size_t)min(n0 + i * 16 + r16, P.N - 1) * P.ldb + kq * 8;
-    }
-    floatx4 acc[2][2];
+    for (int i = 0; i < F; ++i)
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int j = 0; j < F; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (cnt > 0) {
+        // a load takes 64 contiguous bytes of a row by four consecutive lanes
+        const int lr = lane >> 2, lp = lane & 3;
+        const E *pa[F], *pb[F];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const int nk = P.K / 32;
-    switch (nk) {   // the products in use have 4, 16 or 32 k-steps
-    case 4: kloop_fixed<4, PF>(pa, pb, acc); break;
-    case 16: kloop_fixed<16, PF>(pa, pb, acc); break;
-    case 32: kloop_fixed<32, PF>(pa, pb, acc); break;
-    default: kloop_any<PF>(pa, pb, acc, nk); break;
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
-            epi4<true>(P, m0 + i * 16 + kq * 4, n0 + j * 16 + r16, v);
+        for (int i = 0; i < F; ++i) {
+            pa[i] = (const E *)P.A + (size_t)min(m0 + i * 16 + lr, P.M - 1) * P.lda + wave * KB +
+                    lp * (16 / (int)sizeof(E));
+            pb[i] = (const E *)P.B + (size_t)min(n0 + i * 16 + lr, P.N - 1) * P.ldb + wave * KB +
+                    lp * (16 / (int)sizeof(E));
         }
+        // and goes through 1 KiB of this wave's LDS to the MFMA's lanes (LDS
+        // operations of one wave complete in order: no barrier).  Piece p of
+        // row r sits at p ^ (r / 4), so neither side has bank conflicts.
+        char *stage = (char *)&red[0][0][0] + wave * (2 * F * 1024);
+        const int st = lr * 64 + ((lp ^ (lr >> 2)) * 16);
+        const int ld = r16 * 64 + ((kq ^ (r16 >> 2)) * 16);
+        static_assert(2 * F * 1024 <= sizeof(red[0]), "a wave's fragments fit its partial block");
+        frag ra[D][F], rb[D][F];
+        // block q of this wave (past the last: the last again, never used)
+        auto load = [&](frag (&xa)[F], frag (&xb)[F], int q) {
+            const int off = min(q, cnt - 1) * (NW * KB);
+#pragma unroll
+            for (int i = 0; i < F; ++i) {
+                xa[i] = *(const frag *)(pa[i] + off);
+                xb[i] = *(const frag *)(pb[i] + off);
+            }
+        };
+        auto mma = [&](const frag (&la)[F], const frag (&lb)[F]) {
+            frag xa[F], xb[F];
+#pragma unroll
+            for (int i = 0; i < F; ++i) {
+                *(frag *)(stage + i * 1024 + st) = la[i];
+                *(frag *)(stage + (F + i) * 1024 + st) = lb[i];
+            }
+#pragma unroll
+            for (int i = 0; i < F; ++i) {
+                xa[i] = *(const frag *)(stage + i * 1024 + ld);
+                xb[i] = *(const frag *)(stage + (F + i) * 1024 + ld);
+            }
+            if constexpr (BF) {
+#pragma unroll
+                for (int i = 0; i < F; ++i)
+#pragma unroll
+                    for (int j = 0; j < F; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xa[i], xb[j], acc[i][j],
+                                                                            0, 0, 0);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int i = 0; i < F; ++i)
+#pragma unroll
+                        for (int j = 0; j < F; ++j)
+                            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[i][e], xb[j][e],
+                                                                             acc[i][j], 0, 0, 0);
+            }
+        };
+        static_for<0, D>([&](auto q) { load(ra[q], rb[q], q); });
+        int k = 0;
+        for (; k + D <= cnt; k += D)
+            static_for<0, D>([&](auto q) {
+                mma(ra[q], rb[q]);
+                load(ra[q], rb[q], k + q + D);
+                // keep the refill here, D blocks ahead of its use
+                __builtin_amdgcn_sched_barrier(0);
+            });
+        static_for<0, D - 1>([&](auto q) {
+            if (k + q < cnt) mma(ra[q], rb[q]);
+        });
+    }
+    // the staged fragments span every wave's part of red
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < F; ++i)
+#pragma unroll
+        for (int j = 0; j < F; ++j)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) red[wave][i * 16 + kq * 4 + e][j * 16 + r16] = acc[i][j][e];
+    __syncthreads();
+    auto sum = [&](int r, int c) {
+        float v = red[0][r][c];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) v += red[w][r][c];
+        return v;
+    };
+    if (P.mode == EPI_GRAD || P.mode == EPI_BIAS) {
+        // row-major, a row of T columns by T consecutive threads
+        const int ncol = P.mode == EPI_GRAD ? min(P.N, P.gcols) : P.N;
+#pragma unroll
+        for (int g = 0; g < T * T / NT; ++g) {
+            const int q = tid + NT * g, r = q / T, c = q % T;
+            const int row = m0 + r, col = n0 + c;
+            if (row >= P.M || col >= ncol) continue;
+            float v = sum(r, c);
+            if (P.mode == EPI_BIAS) {
+                v += col < P.bsplit ? P.bias0[col] : P.bias1[col - P.bsplit];
+                ((float *)P.out)[(size_t)row * P.ldo + col] = v;
+            } else {
+                float *d = row < P.gsplit ? P.g0 + (size_t)row * P.ldg
+                                          : P.g1 + (size_t)(row - P.gsplit) * P.ldg;
+                d[col] = v;
+            }
+        }
+        return;
+    }
+    // activations and their gradients: four rows of one column a thread (the
+    // transposed rows of outT and hsrc are contiguous), then row-major
+    // through the first partial's block
+    typedef E e4 __attribute__((ext_vector_type(4)));
+    constexpr int NG = T * T / 4, G = (NG + NT - 1) / NT;
+    e4 h[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const int q = tid + NT * g, c = q / (T / 4), r = q % (T / 4) * 4;
+        if (q >= NG) break;
+        const int row = min(m0 + r, P.M - 4), col = min(n0 + c, P.N - 1);
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = sum(r + e, c);
+        if (P.mode == EPI_TANH) {
+            const float b = col < P.bsplit ? P.bias0[col] : P.bias1[col - P.bsplit];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) h[g][e] = to_elem<BF>(fast_tanh(v[e] + b));
+        } else {
+            const e4 y4 = *(const e4 *)((const E *)P.hsrc + (size_t)col * P.ldh + row);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float y = (float)y4[e];
+                h[g][e] = to_elem<BF>(v[e] * (1.0f - y * y));
+            }
+        }
+        if (P.outT && m0 + r < P.M && n0 + c < P.N)
+            *(e4 *)((E *)P.outT + (size_t)col * P.ldt + row) = h[g];
+    }
+    if (!P.out) return;
+    __syncthreads();
+    E(*hs)[PITCH] = (E(*)[PITCH])&red[0][0][0];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const int q = tid + NT * g, c = q / (T / 4), r = q % (T / 4) * 4;
+        if (q >= NG) break;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) hs[r + e][c] = h[g][e];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+        const int q = tid + NT * g, r = q / (T / 4), c = q % (T / 4) * 4;
+        if (q >= NG || m0 + r >= P.M || n0 + c >= P.N) continue;
+        e4 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[e] = hs[r][c + e];
+        *(e4 *)((E *)P.out + (size_t)(m0 + r) * P.ldo + n0 + c) = o;
+    }
 }
 
 // bf16 through LDS, for products whose K is a multiple of 128 (all of the
@@ -373,7 +399,7 @@ constexpr int LTHREADS = LWAVES * WAVE;
 // LDS (row-major and transposed), and a group of G threads stores whole
 // rows of it: 128 contiguous bytes per bf16 row, 256 per fp32 row, 16
 // bytes a thread where the output's rows are 16-byte aligned, else one
-// element a thread, a row per 64 threads.  Same values as epi4, same bits.
+// element a thread, a row per 64 threads.
 constexpr int ER = 64 + 8;   // LDS row of a staged bf16 block (elements)
 constexpr int EF = 64 + 4;   // LDS row of a staged fp32 block (floats)
 constexpr int STAGE_BYTES = 2 * 64 * ER * 2;   // one block: T and R (F is smaller)
@@ -566,15 +592,12 @@ __global__ __launch_bounds__(LTHREADS, 2) void gemm_lds_kernel(GemmBatch gb)
     case 1: lds_kloop<1>(ga, gbp, P.lda, P.ldb, Mr, Nr, smem, acc); break;
     case 4: lds_kloop<4>(ga, gbp, P.lda, P.ldb, Mr, Nr, smem, acc); break;
     case 8: lds_kloop<8>(ga, gbp, P.lda, P.ldb, Mr, Nr, smem, acc); break;
-    default: break;   // the launcher routes other K to gemm_bf16_kernel
+    default: break;   // the launcher routes other K to gemm_split_kernel
     }
     const int wm = m0 + (wave >> 2) * 32, wn = n0 + (wave & 3) * 16;
     if (P.mode == EPI_BIAS) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const float v[4] = {acc[i][0], acc[i][1], acc[i][2], acc[i][3]};
-            epi4<true>(P, wm + i * 16 + kq * 4, wn + r16, v);
-        }
+        for (int i = 0; i < 2; ++i) bias4(P, wm + i * 16 + kq * 4, wn + r16, acc[i]);
         return;
     }
     static_assert(STAGE_BYTES <= sizeof(smem), "the staged block fits");
@@ -721,10 +744,7 @@ __global__ __launch_bounds__(BTHREADS, 1) void gemm_big_kernel(GemmBatch gb)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const float v[4] = {acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]};
-                epi4<true>(P, wm + i * 16 + kq * 4, wn + j * 16 + r16, v);
-            }
+            for (int j = 0; j < 4; ++j) bias4(P, wm + i * 16 + kq * 4, wn + j * 16 + r16, acc[i][j]);
         return;
     }
     // each wave stages its 64 x 64 block in LDS (free once every wave has
@@ -744,53 +764,6 @@ __global__ __launch_bounds__(BTHREADS, 1) void gemm_big_kernel(GemmBatch gb)
                    i * 16 + (el >> 4) * 4, j * 16 + (el & 15), blk);
     __syncthreads();
     store_staged<WAVE>(P, blk, wm, wn, el);
-}
-
-// fp32: 16x16 threads, each a 4x4 block of the 64x64 tile; k-slices of 16
-// staged in LDS, k-major, so the inner loop reads broadcast-free rows.
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmBatch gb)
-{
-    __shared__ float As[16][GT + 4];
-    __shared__ float Bs[16][GT + 4];
-    int agent, t;
-    if (!gemm_slot(gb, agent, t)) return;
-    const int pi = find_prob(gb, t);
-    const GemmProb P = agent_prob(gb, pi, agent);
-    t -= P.tile0;
-    const int tn = __builtin_amdgcn_readfirstlane(t % P.tiles_n);
-    const int tm = __builtin_amdgcn_readfirstlane(t / P.tiles_n);
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
-    const float *A = (const float *)P.A, *B = (const float *)P.B;
-    // loader: row lr = tid / 4 of the tile, k-quad lq = tid % 4
-    const int lr = tid >> 2, lq = tid & 3;
-    const float *la = A + (size_t)min(tm * GT + lr, P.M - 1) * P.lda + lq * 4;
-    const float *lb = B + (size_t)min(tn * GT + lr, P.N - 1) * P.ldb + lq * 4;
-    float acc[4][4] = {};
-    for (int k = 0; k < P.K; k += 16) {
-        const floatx4 va = *(const floatx4 *)(la + k);
-        const floatx4 vb = *(const floatx4 *)(lb + k);
-        __syncthreads();
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            As[lq * 4 + e][lr] = va[e];
-            Bs[lq * 4 + e][lr] = vb[e];
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < 16; ++kk) {
-            const floatx4 a = *(const floatx4 *)&As[kk][ty * 4];
-            const floatx4 b = *(const floatx4 *)&Bs[kk][tx * 4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-        }
-    }
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float v[4] = {acc[0][j], acc[1][j], acc[2][j], acc[3][j]};
-        epi4<false>(P, tm * GT + ty * 4, tn * GT + tx * 4 + j, v);
-    }
 }
 
 // Minibatch indices outside [0, rows) are clamped into it (never read out
@@ -1513,7 +1486,7 @@ hipError_t run_gemms(bool bf, const Agents &ag, std::initializer_list<GemmProb> 
         tiles_big += cdiv(p.M, BT) * cdiv(p.N, BT);
     }
     big = big && tiles_big * ag.n >= BIG_MIN_TILES;
-    const int TN = big ? BT : GT, TM = big ? BM : GT;
+    const int TN = big ? BT : staged ? GT : ST, TM = big ? BM : staged ? GT : ST;
     int tiles = 0;
     for (const GemmProb &p : ps) {
         GemmProb q = p;
@@ -1527,8 +1500,10 @@ hipError_t run_gemms(bool bf, const Agents &ag, std::initializer_list<GemmProb> 
     const dim3 grid(8 * cdiv(tiles * ag.n, 8));
     if (big) hipLaunchKernelGGL(gemm_big_kernel, grid, dim3(BTHREADS), 0, s, gb);
     else if (staged) hipLaunchKernelGGL(gemm_lds_kernel, grid, dim3(LTHREADS), 0, s, gb);
-    else if (bf) hipLaunchKernelGGL(gemm_bf16_kernel, grid, dim3(256), 0, s, gb);
-    else hipLaunchKernelGGL(gemm_f32_kernel, grid, dim3(256), 0, s, gb);
+    else if (bf) hipLaunchKernelGGL((gemm_split_kernel<true, ST / 16, SWAVES, SD>), grid,
+                                    dim3(SWAVES * WAVE), 0, s, gb);
+    else hipLaunchKernelGGL((gemm_split_kernel<false, ST / 16, SWAVES, SD>), grid, dim3(SWAVES * WAVE), 0,
+                            s, gb);
     return hipGetLastError();
 }
 

@@ -388,3 +388,19 @@ def test_partial_column_blocks_in_staged_products():
     for a in range(A):
         assert torch.equal(ga[a], grad), a
         assert torch.equal(pa[a], prm) and torch.equal(ma[a], m) and torch.equal(va[a], v), a
+
+
+@pytest.mark.parametrize("n,hidden,B,dtype", [
+    (5, (32, 32), 32, "f32"),        # K = 32: two k-blocks for four waves
+    (7, (96, 224), 160, "f32"),      # ragged tiles: 43 inputs, 7 actions, odd block counts
+    (33, (288, 64), 96, "f32"),      # action columns past one tile
+    (5, (32, 32), 32, "bf16"),       # K = 32: one k-block
+    (7, (96, 224), 160, "bf16"),
+    (33, (288, 64), 96, "bf16"),
+])
+def test_products_split_over_the_waves(n, hidden, B, dtype):
+    """Shapes at the edges of the 32 x 32 tiles and of the waves' shares of
+    K, against the oracle's gradient."""
+    cfg = W.get_config("tiny").with_(name=f"split-{n}", n=n, hidden=hidden, dtype=dtype)
+    r = _run(cfg, 2 * B, B, 1)
+    _check_grad(r["dims"], r["grad"], r["g_o"], GRAD_TOL[dtype], f"{n} {hidden} {B} {dtype}")
