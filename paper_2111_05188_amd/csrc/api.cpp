@@ -289,21 +289,22 @@ bool critic_layout(const tp_critic *c, CriticLayout *L)
     L->K_pad = (L->S + 31) / 32 * 32;
     L->mfma = critic_mfma_shape(*L);
     size_t off = 0;
-    const int outs[2] = {L->H1, L->H2}, ins[2] = {L->K_pad, L->H1};
+    const int kb = c->dtype == TP_BF16 ? 32 : 16;   // inputs per k-step
+    L->KS[0] = L->K_pad / kb;
+    L->KS[1] = (L->H1 + kb - 1) / kb;
+    // layer 1 fills layer 2's whole k-steps (zero weights and biases past H1)
+    L->NT[0] = L->KS[1] * kb / 16;
+    L->NT[1] = (L->H2 + 15) / 16;
     for (int l = 0; l < 2; ++l) {
-        L->NT[l] = (outs[l] + 15) / 16;
-        L->KS[l] = ins[l] / 32;
-        const size_t wbytes = L->mfma ? (size_t)L->NT[l] * L->KS[l] * 64 * 16
-                                      : (size_t)ins[l] * outs[l] * 4;
         L->off_W[l] = off;
-        off = al(off + wbytes);
+        off = al(off + (size_t)L->NT[l] * L->KS[l] * 1024);
     }
     L->off_W[2] = off;
-    off = al(off + (size_t)L->H2 * 4);
+    off = al(off + (size_t)L->NT[1] * 64);
     L->off_b[0] = off;
-    off = al(off + (size_t)L->H1 * 4);
+    off = al(off + (size_t)L->NT[0] * 64);
     L->off_b[1] = off;
-    off = al(off + (size_t)L->H2 * 4);
+    off = al(off + (size_t)L->NT[1] * 64);
     L->off_b[2] = off;
     off = al(off + 4);
     L->agent_stride = off;

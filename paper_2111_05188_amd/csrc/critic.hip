@@ -19,9 +19,10 @@
 // groups of a tile, then across the eight waves in LDS, always in the same
 // order, so the result is deterministic.
 //
-// Generic kernel (fp32, or bf16 shapes the MFMA kernel does not take):
-// 16 rows per workgroup, one thread per output unit, weights transposed so
-// consecutive threads read consecutive addresses.
+// Every other shape (fp32, or bf16 of other widths) runs the tile kernel
+// below.
+#include <type_traits>
+
 #include "device.hpp"
 #include "internal.hpp"
 
@@ -257,81 +258,216 @@ __global__ __launch_bounds__(NW *WAVE, CRITIC_MIN_WAVES) void critic_mfma_kernel
     }
 }
 
-// Generic kernel: 16 rows, 256 threads, fp32 arithmetic on the (bf16-
-// rounded, for TP_BF16) transposed weights W1T [K_pad][H1], W2T [H1][H2].
-constexpr int GEN_BM = 16;
-constexpr int GEN_THREADS = 256;
+// ---------------------------------------------------------------------------
+// Every other shape (fp32, or bf16 of other widths): the tile kernel.
+//
+// A workgroup takes BM = 16 RT rows of one agent, numbered over its (step,
+// env) pairs, so few envs per agent still fill the tiles.  Weights are
+// MFMA fragments of 1 KiB ([tile of 16 outputs][k-block][64 lanes][16
+// bytes]; a k-block is 16 fp32 or 32 bf16 inputs) streamed from L2 D blocks
+// ahead; rows and the first hidden layer sit in LDS.  A wave owns OT output
+// tiles at a time, OT x RT accumulators.  fp32 takes
+// v_mfma_f32_16x16x4_f32, MFMA e on element e of every lane's 16 bytes.
+// Where one round of the waves covers layer 1, the hidden rows take the
+// observation rows' place (a third workgroup then fits a CU).
+//
+// fp32 is bound by its MFMAs: a year of the 30-stock daily workload (253 x
+// 1,024 rows, 301-256-256) takes 0.70 ms, 105 TFLOP/s of the 153 a large
+// fp32 product reaches; 0.68 ms without the tanh.  The kernel before it (one
+// VALU thread an output, 16 rows a workgroup) took 2.26 ms, and 2.21 ms with
+// bf16 rows, where this one takes 0.18 (1.00 against 0.11 at 298-128-352,
+// 21.6 against 0.46 at 1001-768-768).  D weight blocks in flight: 2 for
+// fp32 (4: 1% slower), 4 for bf16 (2: 5% slower, 8: 80%).  Two workgroups a
+// CU, without the shared place: 0.75 ms; eight waves a workgroup: 0.71.
+// ---------------------------------------------------------------------------
+template <bool BF>
+struct TileType {
+    typedef float E;
+};
+template <>
+struct TileType<true> {
+    typedef __bf16 E;
+};
 
-template <bool BF16>
-__global__ __launch_bounds__(GEN_THREADS) void critic_generic_kernel(CriticArgs A)
+constexpr int TILE_NW = 4;   // waves per workgroup
+
+// One layer for this wave's tiles: h = tanh(W x + b) into hs, or, for the
+// LAST one, part[rt] += w3 . h of this lane's outputs.
+template <bool BF, int RT, int NW, int OT, bool LAST>
+__device__ __forceinline__ void tile_layer(const uint8_t *W, const float *bias, const float *w3,
+                                           int NT, int KB, const uint8_t *xs, int ldx, uint8_t *hs,
+                                           int ldh, float (&part)[RT], bool over, int wave, int lane)
 {
+    typedef typename TileType<BF>::E E;
+    typedef E frag __attribute__((ext_vector_type(16 / sizeof(E))));
+    typedef E e4 __attribute__((ext_vector_type(4)));
+    constexpr int D = BF ? 4 : 2;
+    const int r16 = lane & 15, kq = lane >> 4;
+    const uint8_t *xb = xs + r16 * ldx + kq * 16;
+    // `over`: hs takes xs's place, which every wave has read by the barrier
+    // (one round; a wave without tiles computes the last one for nothing)
+    for (int g0 = wave * OT; g0 < NT || over; g0 += NW * OT) {
+        const uint8_t *wt[OT];
+#pragma unroll
+        for (int t = 0; t < OT; ++t) wt[t] = W + (size_t)min(g0 + t, NT - 1) * KB * 1024 + lane * 16;
+        floatx4 acc[OT][RT];
+#pragma unroll
+        for (int t = 0; t < OT; ++t)
+#pragma unroll
+            for (int r = 0; r < RT; ++r) acc[t][r] = floatx4{0.f, 0.f, 0.f, 0.f};
+        frag w[D][OT];
+        auto load = [&](frag (&x)[OT], int k) {   // past the last block: the last again
+            const int off = min(k, KB - 1) * 1024;
+#pragma unroll
+            for (int t = 0; t < OT; ++t) x[t] = *(const frag *)(wt[t] + off);
+        };
+        auto mma = [&](const frag (&x)[OT], int k) {
+            frag v[RT];
+#pragma unroll
+            for (int r = 0; r < RT; ++r) v[r] = *(const frag *)(xb + r * 16 * ldx + k * 64);
+            if constexpr (BF) {
+#pragma unroll
+                for (int r = 0; r < RT; ++r)
+#pragma unroll
+                    for (int t = 0; t < OT; ++t)
+                        acc[t][r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[t], v[r], acc[t][r], 0,
+                                                                            0, 0);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int r = 0; r < RT; ++r)
+#pragma unroll
+                        for (int t = 0; t < OT; ++t)
+                            acc[t][r] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[t][e], v[r][e],
+                                                                             acc[t][r], 0, 0, 0);
+            }
+        };
+#pragma unroll
+        for (int d = 0; d < D; ++d) load(w[d], d);
+        int k = 0;
+        for (; k + D <= KB; k += D)
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                mma(w[d], k + d);
+                load(w[d], k + d + D);
+                __builtin_amdgcn_sched_barrier(0);   // the refill stays here
+            }
+#pragma unroll
+        for (int d = 0; d < D - 1; ++d)
+            if (k + d < KB) mma(w[d], k + d);
+        if (over) __syncthreads();
+#pragma unroll
+        for (int t = 0; t < OT; ++t) {
+            if (g0 + t >= NT) break;
+            const int o = (g0 + t) * 16 + kq * 4;
+            const floatx4 bv = *(const floatx4 *)(bias + o);
+            floatx4 wv;
+            if (LAST) wv = *(const floatx4 *)(w3 + o);
+#pragma unroll
+            for (int r = 0; r < RT; ++r) {
+                e4 h;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) h[e] = (E)tanh_f32(acc[t][r][e] + bv[e]);
+                if (LAST) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) part[r] = fmaf(wv[e], (float)h[e], part[r]);
+                } else {
+                    *(e4 *)(hs + (r * 16 + r16) * ldh + o * (int)sizeof(E)) = h;
+                }
+            }
+        }
+        if (over) break;
+    }
+}
+
+// tiles a wave takes at a time: the fewest tile slots over its rounds
+__device__ __forceinline__ int tiles_per_wave(int NT, int NW)
+{
+    int best = 4, cost = 1 << 30;
+    for (int ot = 4; ot >= 1; --ot) {
+        const int c = (NT + NW * ot - 1) / (NW * ot) * ot;
+        if (c < cost) {
+            cost = c;
+            best = ot;
+        }
+    }
+    return best;
+}
+
+template <bool BF, int RT, int NW>
+__global__ __launch_bounds__(NW *WAVE) void critic_tile_kernel(CriticArgs A, int ldx, int ldh,
+                                                                 int over)
+{
+    typedef typename TileType<BF>::E E;
+    constexpr int BM = 16 * RT, NTH = NW * WAVE, VE = 16 / (int)sizeof(E);
     extern __shared__ __align__(16) uint8_t smem[];
     const CriticLayout &P = A.lay;
-    const int S = P.S, K = P.K_pad, H1 = P.H1, H2 = P.H2;
-    float *xs = (float *)smem;                 // [GEN_BM][K]
-    float *h1 = xs + GEN_BM * K;               // [GEN_BM][H1]
-    float *red = h1 + GEN_BM * H1;             // [GEN_THREADS][GEN_BM]
-    const int tid = threadIdx.x;
-    const RowBlock rb = row_block(A, GEN_BM);
-    const uint8_t *pk = A.packed + (size_t)rb.agent * P.agent_stride;
-    const float *W1T = (const float *)(pk + P.off_W[0]);
-    const float *W2T = (const float *)(pk + P.off_W[1]);
-    const float *w3 = (const float *)(pk + P.off_W[2]);
-    const float *b1 = (const float *)(pk + P.off_b[0]);
-    const float *b2 = (const float *)(pk + P.off_b[1]);
+    // rows and hidden rows (byte pitches); with `over` these in the place of those
+    uint8_t *xs = smem, *hs = over ? xs : xs + BM * ldx;
+    float *vred = (float *)(over ? xs + BM * max(ldx, ldh) : hs + BM * ldh);   // [NW][BM]
+    const int tid = threadIdx.x, lane = tid % WAVE;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / WAVE);
+    // rows r0 .. r0 + BM - 1 of the agent's T epa rows (step r / epa, env r % epa)
+    const int epa = A.envs_per_agent;
+    const int64_t R = A.T * epa, bpa = (R + BM - 1) / BM;
+    const int agent = (int)(blockIdx.x / bpa);
+    const int64_t r0 = (int64_t)(blockIdx.x % bpa) * BM;
+    const int nrow = (int)min((int64_t)BM, R - r0);
+    const int64_t t0 = r0 / epa;
+    const int e0 = (int)(r0 % epa);
+    auto row_of = [&](int r) {   // row r of the block in the [T][E] arrays
+        const uint32_t x = (uint32_t)e0 + (uint32_t)r, t = x / (uint32_t)epa;
+        return (t0 + t) * A.E + (int64_t)agent * epa + (x - t * (uint32_t)epa);
+    };
+    const uint8_t *pk = A.packed + (size_t)agent * P.agent_stride;
 
-    for (int i = tid; i < GEN_BM * K; i += GEN_THREADS) {
-        const int r = i / K, k = i % K;
-        float v = 0.f;
-        if (r < rb.nrow && k < S) {
-            const size_t at = ((size_t)rb.t * A.E + rb.e0 + r) * A.ld_obs + k;
-            v = BF16 ? (float)((const __bf16 *)A.obs)[at] : ((const float *)A.obs)[at];
-        }
-        xs[i] = v;
+    // observation rows into LDS, zeros from column S on
+    const int pieces = P.K_pad / VE, S = P.S;
+    for (int i = tid; i < BM * pieces; i += NTH) {
+        const int r = i / pieces, c = i % pieces;
+        typedef E pv __attribute__((ext_vector_type(16 / sizeof(E))));
+        pv v = *(const pv *)((const E *)A.obs + (size_t)row_of(min(r, nrow - 1)) * A.ld_obs + c * VE);
+        if (c * VE + VE > S)
+#pragma unroll
+            for (int e = 0; e < VE; ++e)
+                if (c * VE + e >= S) v[e] = (E)0.f;
+        *(pv *)(xs + r * ldx + c * 16) = v;
     }
     __syncthreads();
-    for (int o = tid; o < H1; o += GEN_THREADS) {
-        float acc[GEN_BM];
+    const float *b1 = (const float *)(pk + P.off_b[0]), *b2 = (const float *)(pk + P.off_b[1]);
+    const float *w3 = (const float *)(pk + P.off_W[2]);
+    float part[RT];
 #pragma unroll
-        for (int r = 0; r < GEN_BM; ++r) acc[r] = 0.f;
-        for (int k = 0; k < S; ++k) {
-            const float wk = W1T[(size_t)k * H1 + o];
-#pragma unroll
-            for (int r = 0; r < GEN_BM; ++r) acc[r] = fmaf(wk, xs[r * K + k], acc[r]);
+    for (int r = 0; r < RT; ++r) part[r] = 0.f;
+    auto layer = [&](auto last, int l, const float *b, const uint8_t *x, int ld) {
+        constexpr bool LAST = decltype(last)::value;
+        const uint8_t *W = pk + P.off_W[l];
+        const int NT = P.NT[l], KB = P.KS[l];
+        switch (tiles_per_wave(NT, NW)) {
+        case 1: tile_layer<BF, RT, NW, 1, LAST>(W, b, w3, NT, KB, x, ld, hs, ldh, part, !LAST && over, wave, lane); break;
+        case 2: tile_layer<BF, RT, NW, 2, LAST>(W, b, w3, NT, KB, x, ld, hs, ldh, part, !LAST && over, wave, lane); break;
+        case 3: tile_layer<BF, RT, NW, 3, LAST>(W, b, w3, NT, KB, x, ld, hs, ldh, part, !LAST && over, wave, lane); break;
+        default: tile_layer<BF, RT, NW, 4, LAST>(W, b, w3, NT, KB, x, ld, hs, ldh, part, !LAST && over, wave, lane); break;
         }
-#pragma unroll
-        for (int r = 0; r < GEN_BM; ++r) {
-            const float h = tanhf(acc[r] + b1[o]);
-            h1[r * H1 + o] = BF16 ? (float)to_bf16(h) : h;
-        }
-    }
+    };
+    layer(std::false_type{}, 0, b1, xs, ldx);
     __syncthreads();
-    float part[GEN_BM];
+    layer(std::true_type{}, 1, b2, hs, ldh);
 #pragma unroll
-    for (int r = 0; r < GEN_BM; ++r) part[r] = 0.f;
-    for (int o = tid; o < H2; o += GEN_THREADS) {
-        float acc[GEN_BM];
-#pragma unroll
-        for (int r = 0; r < GEN_BM; ++r) acc[r] = 0.f;
-        for (int k = 0; k < H1; ++k) {
-            const float wk = W2T[(size_t)k * H2 + o];
-#pragma unroll
-            for (int r = 0; r < GEN_BM; ++r) acc[r] = fmaf(wk, h1[r * H1 + k], acc[r]);
-        }
-#pragma unroll
-        for (int r = 0; r < GEN_BM; ++r) {
-            float h = tanhf(acc[r] + b2[o]);
-            if (BF16) h = (float)to_bf16(h);
-            part[r] = fmaf(w3[o], h, part[r]);
-        }
+    for (int r = 0; r < RT; ++r) {
+        part[r] += __shfl_xor(part[r], 16);
+        part[r] += __shfl_xor(part[r], 32);
     }
+    if (lane < 16)
 #pragma unroll
-    for (int r = 0; r < GEN_BM; ++r) red[tid * GEN_BM + r] = part[r];
+        for (int r = 0; r < RT; ++r) vred[wave * BM + r * 16 + lane] = part[r];
     __syncthreads();
-    if (tid < rb.nrow) {
+    if (tid < nrow) {
         float v = *(const float *)(pk + P.off_b[2]);
-        for (int th = 0; th < GEN_THREADS; ++th) v += red[th * GEN_BM + tid];
-        A.value[(size_t)rb.t * A.E + rb.e0 + tid] = v;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) v += vred[w * BM + tid];
+        A.value[row_of(tid)] = v;
     }
 }
 
@@ -346,6 +482,44 @@ hipError_t launch_with_lds(K k, size_t nblk, int threads, size_t lds, const Crit
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k, dim3((unsigned)nblk), dim3(threads), lds, s, a);
     return hipGetLastError();
+}
+
+template <bool BF, int RT, int NW>
+hipError_t launch_tile_cfg(const CriticArgs &a, int ldx, int ldh, int over, size_t lds, hipStream_t s)
+{
+    const int64_t R = a.T * a.envs_per_agent, nblk = (R + 16 * RT - 1) / (16 * RT) * a.n_agents;
+    if (lds > LDS_LIMIT || nblk > 0x7fffffffLL) return hipErrorInvalidConfiguration;
+    auto k = critic_tile_kernel<BF, RT, NW>;
+    const hipError_t e = hipFuncSetAttribute((const void *)k,
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k, dim3((unsigned)nblk), dim3(NW * WAVE), lds, s, a, ldx, ldh, over);
+    return hipGetLastError();
+}
+
+template <bool BF>
+hipError_t launch_tile(const CriticArgs &a, hipStream_t s)
+{
+    const CriticLayout &L = a.lay;
+    const int esz = BF ? 2 : 4;
+    // 16 bytes past whole k-blocks: rows 4 banks apart
+    const int ldx = L.K_pad * esz + 16, ldh = L.KS[1] * 64 + 16;
+    constexpr int NW = TILE_NW;
+    const int over = L.NT[0] <= 4 * NW;
+    auto lds = [&](int rt) {
+        return (size_t)16 * rt * ((over ? (ldx > ldh ? ldx : ldh) : ldx + ldh) + NW * 4);
+    };
+    const auto blocks = [&](int rt) {
+        return (a.T * a.envs_per_agent + 16 * rt - 1) / (16 * rt) * a.n_agents;
+    };
+    // the largest row tile with three workgroups' LDS on a CU (fragments are
+    // used RT times) that still leaves two workgroups for every CU
+    for (int rt : {4, 2}) {
+        if (lds(rt) > LDS_LIMIT / 3 || blocks(rt) < 512) continue;
+        if (rt == 4) return launch_tile_cfg<BF, 4, NW>(a, ldx, ldh, over, lds(rt), s);
+        return launch_tile_cfg<BF, 2, NW>(a, ldx, ldh, over, lds(rt), s);
+    }
+    return launch_tile_cfg<BF, 1, NW>(a, ldx, ldh, over, lds(1), s);
 }
 
 }  // namespace
@@ -372,11 +546,8 @@ hipError_t launch_critic_value(const CriticArgs &a, hipStream_t s)
         return launch_with_lds(critic_mfma_kernel<NW, T1024, CRITIC_ACC_TILES / T1024, 32>, nblk,
                                NW * WAVE, lds, a, s);
     }
-    const size_t nblk = (size_t)a.T * a.n_agents * ((a.envs_per_agent + GEN_BM - 1) / GEN_BM);
-    const size_t lds = ((size_t)GEN_BM * (L.K_pad + L.H1) + (size_t)GEN_THREADS * GEN_BM) * 4;
-    if (L.dtype == TP_BF16)
-        return launch_with_lds(critic_generic_kernel<true>, nblk, GEN_THREADS, lds, a, s);
-    return launch_with_lds(critic_generic_kernel<false>, nblk, GEN_THREADS, lds, a, s);
+    if (L.dtype == TP_BF16) return launch_tile<true>(a, s);
+    return launch_tile<false>(a, s);
 }
 
 }  // namespace tpk

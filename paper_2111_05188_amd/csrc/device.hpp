@@ -135,4 +135,19 @@ __device__ __forceinline__ float tanh_from_e2(float e2)
     return fmaf(2.0f, __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(e2)), -1.0f);
 }
 
+// tanh to fp32 precision (about 2 ulp; NaN stays NaN) without a branch: one
+// quotient N / D, from Lambert's continued fraction x / (1 + x^2 / (3 + x^2 /
+// (5 + x^2 / (7 + x^2 / 9)))) where |x| < 0.625 (cut off there, it is within
+// 1e-9 of tanh, relative), from (e - 1) / (e + 1), e = exp(2 |x|) >= 3.49,
+// above, where the subtraction loses nothing; past 10 tanh is 1 in fp32.
+__device__ __forceinline__ float tanh_f32(float x)
+{
+    const float ax = fabsf(x), x2 = x * x;
+    const float e = __builtin_amdgcn_exp2f(-NEG_2LOG2E * (ax > 10.0f ? 10.0f : ax));
+    const bool small = ax < 0.625f;
+    const float num = small ? x * fmaf(x2, x2 + 105.0f, 945.0f) : copysignf(e - 1.0f, x);
+    const float den = small ? fmaf(x2, fmaf(15.0f, x2, 420.0f), 945.0f) : e + 1.0f;
+    return num * __builtin_amdgcn_rcpf(den);
+}
+
 }  // namespace tpk

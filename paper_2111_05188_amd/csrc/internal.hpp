@@ -115,13 +115,12 @@ hipError_t launch_gae(const float *r, const float *v, const uint8_t *d, int L,
 hipError_t launch_pack(const tp_actor *a, const PackedLayout &lay, void *dst,
                        hipStream_t s);
 
-// Byte layout of one agent's packed critic inside the packed buffer.
-//  mfma (bf16, H1 == H2 in {512, 1024}, K_pad % 128 == 0): W1, W2 as MFMA
-//       A-fragments [NT][KS][64 lanes][8 bf16] (as the actor's);
-//  otherwise: W1T [K_pad][H1] and W2T [H1][H2] fp32 transposes (values
-//       rounded to bf16 for a bf16 critic), zero rows for k >= S.
-//  Then w3 [H2] fp32 (rounded to bf16 for a bf16 critic), b1 [H1],
-//  b2 [H2], b3 [1] fp32.
+// Byte layout of one agent's packed critic inside the packed buffer: W1 and
+// W2 as MFMA A-fragments of 1 KiB, [NT][KS][64 lanes][16 bytes] (bf16: as
+// the actor's; fp32: lane l of tile t, k-step s holds W[16t + l%16][16s +
+// 4(l/16) + 0..3]), zero outside the matrix; then w3 (rounded to bf16 for a
+// bf16 critic), b1, b2 in whole tiles (zeros past the width) and b3, fp32.
+// mfma: bf16, H1 == H2 in {512, 1024}, K_pad == 1024.
 struct CriticLayout {
     int dtype;
     int S, H1, H2, K_pad;

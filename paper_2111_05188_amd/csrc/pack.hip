@@ -55,17 +55,20 @@ __global__ void pack_vec_bf16_kernel(const float *__restrict__ src, int cnt,
         dst[i] = i < cnt ? (float)to_bf16(src[i]) : 0.0f;
 }
 
-// Transpose: element (k, o) of [K][out] is W[o][k] (rounded to bf16 if
-// `bf16`), zero for k >= in.
-__global__ void pack_transpose_kernel(const float *__restrict__ W, int out, int in,
-                                      int K, int bf16, float *__restrict__ dst)
+// fp32 MFMA fragments: element (t, b, lane, e) of [NT][KB][64][4] is
+// W[16t + lane%16][16b + 4(lane/16) + e], zero outside [out][in].
+__global__ void pack_frag_f32_kernel(const float *__restrict__ W, int out, int in, int NT, int KB,
+                                     float *__restrict__ dst)
 {
-    const size_t total = (size_t)K * out;
+    const size_t total = (size_t)NT * KB * WAVE * 4;
     for (size_t p = blockIdx.x * (size_t)blockDim.x + threadIdx.x; p < total;
          p += (size_t)gridDim.x * blockDim.x) {
-        const int o = (int)(p % out), k = (int)(p / out);
-        const float w = k < in ? W[(size_t)o * in + k] : 0.0f;
-        dst[p] = bf16 ? (float)to_bf16(w) : w;
+        const int e = (int)(p % 4);
+        const int lane = (int)((p / 4) % WAVE);
+        const size_t tb = p / (4 * WAVE);
+        const int b = (int)(tb % KB), t = (int)(tb / KB);
+        const int o = 16 * t + (lane % 16), k = 16 * b + 4 * (lane / 16) + e;
+        dst[p] = (o < out && k < in) ? W[(size_t)o * in + k] : 0.0f;
     }
 }
 
@@ -78,37 +81,37 @@ static int grid_for(size_t total)
 hipError_t launch_critic_pack(const tp_critic *c, const CriticLayout &L, void *dst,
                               hipStream_t s)
 {
-    const int outs[2] = {L.H1, L.H2}, ins[2] = {L.S, L.H1}, Ks[2] = {L.K_pad, L.H1};
+    const int outs[2] = {L.H1, L.H2}, ins[2] = {L.S, L.H1};
+    const int pads[2] = {16 * L.NT[0], 16 * L.NT[1]};
     uint8_t *base = (uint8_t *)dst;
     for (int ag = 0; ag < c->n_agents; ++ag) {
         uint8_t *pa = base + (size_t)ag * L.agent_stride;
         for (int l = 0; l < 2; ++l) {
             const float *W = c->W[l] + (size_t)ag * (c->agent_stride ? (size_t)c->agent_stride
                                                                      : (size_t)outs[l] * ins[l]);
-            if (L.mfma) {
+            if (L.dtype == TP_BF16) {
                 const size_t tot = (size_t)L.NT[l] * L.KS[l] * WAVE * 8;
                 hipLaunchKernelGGL(pack_bf16_kernel, dim3(grid_for(tot)), dim3(256), 0, s, W,
                                    outs[l], ins[l], L.NT[l], L.KS[l], (__bf16 *)(pa + L.off_W[l]));
             } else {
-                const size_t tot = (size_t)Ks[l] * outs[l];
-                hipLaunchKernelGGL(pack_transpose_kernel, dim3(grid_for(tot)), dim3(256), 0, s, W,
-                                   outs[l], ins[l], Ks[l], (int)(L.dtype == TP_BF16),
-                                   (float *)(pa + L.off_W[l]));
+                const size_t tot = (size_t)L.NT[l] * L.KS[l] * WAVE * 4;
+                hipLaunchKernelGGL(pack_frag_f32_kernel, dim3(grid_for(tot)), dim3(256), 0, s, W,
+                                   outs[l], ins[l], L.NT[l], L.KS[l], (float *)(pa + L.off_W[l]));
             }
-            hipLaunchKernelGGL(pack_vec_kernel, dim3(grid_for(outs[l])), dim3(256), 0, s,
+            hipLaunchKernelGGL(pack_vec_kernel, dim3(grid_for(pads[l])), dim3(256), 0, s,
                                c->b[l] + (size_t)ag * (c->agent_stride ? (size_t)c->agent_stride
                                                                        : (size_t)outs[l]),
-                               outs[l], outs[l],
+                               outs[l], pads[l],
                                (float *)(pa + L.off_b[l]));
         }
         const float *w3 = c->W[2] + (size_t)ag * (c->agent_stride ? (size_t)c->agent_stride
                                                                   : (size_t)L.H2);
         if (L.dtype == TP_BF16)
-            hipLaunchKernelGGL(pack_vec_bf16_kernel, dim3(grid_for(L.H2)), dim3(256), 0, s, w3,
-                               L.H2, L.H2, (float *)(pa + L.off_W[2]));
+            hipLaunchKernelGGL(pack_vec_bf16_kernel, dim3(grid_for(pads[1])), dim3(256), 0, s, w3,
+                               L.H2, pads[1], (float *)(pa + L.off_W[2]));
         else
-            hipLaunchKernelGGL(pack_vec_kernel, dim3(grid_for(L.H2)), dim3(256), 0, s, w3, L.H2,
-                               L.H2, (float *)(pa + L.off_W[2]));
+            hipLaunchKernelGGL(pack_vec_kernel, dim3(grid_for(pads[1])), dim3(256), 0, s, w3, L.H2,
+                               pads[1], (float *)(pa + L.off_W[2]));
         hipLaunchKernelGGL(pack_vec_kernel, dim3(1), dim3(64), 0, s,
                            c->b[2] + (size_t)ag * (c->agent_stride ? (size_t)c->agent_stride : 1), 1, 1,
                            (float *)(pa + L.off_b[2]));

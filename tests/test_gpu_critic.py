@@ -1,7 +1,7 @@
 """GPU parity of tp_critic_value (the PPO critic's forward pass over a
 trajectory's observations) against the oracle's MLP: the bf16 MFMA kernel at
 512- and 1024-wide layers (one agent and several agents, ragged row blocks),
-the generic kernel (fp32 and another bf16 shape), the full 100-stock minute
+the tile kernel (fp32 and other bf16 shapes), the full 100-stock minute
 trajectory shape on sampled rows, and determinism.
 
 Observation blocks [T][E][K_pad] come from the seeded generator
@@ -105,6 +105,32 @@ def test_critic_generic_fp32():
 
 def test_critic_generic_bf16_other_shape():
     _run(W.get_config("dow30").with_(dtype="bf16"), 33, 20)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n,hidden,E,L,A", [
+    (5, (4, 4), 1, 1, 1),             # one row; widths below a tile, one k-block
+    (7, (36, 100), 21, 11, 3),        # seven envs an agent: tiles span steps; ragged widths
+    (5, (260, 268), 90, 99, 2),       # more than one round of tiles: both row buffers
+    (5, (64, 48), 700, 60, 1),        # the largest row tile, a ragged last one
+    (30, (256, 256), 130, 130, 1),    # two row tiles of fp32, four of bf16
+])
+def test_critic_tile_kernel_edges(n, hidden, E, L, A, dtype):
+    cfg = W.get_config("tiny").with_(name=f"tile-{hidden}", n=n, n_ind=8, hidden=hidden,
+                                     dtype=dtype)
+    _run(cfg, E, L, n_agents=A, sample=None if E * L < 4000 else 500)
+
+
+def test_critic_ignores_columns_past_the_state():
+    """Columns S .. K_pad of the rows are ignored, whatever they hold."""
+    cfg = W.get_config("tiny").with_(hidden=(32, 32))
+    crit, obs, values = _run(cfg, 40, 3)
+    v0 = values.clone()
+    obs = obs.clone()
+    obs[:, :, cfg.S:] = float("nan")
+    tp.critic_value(crit, obs, values)
+    torch.cuda.synchronize()
+    assert torch.equal(v0, values)
 
 
 def test_critic_full_nasdaq_trajectory_sampled():
