@@ -12,7 +12,9 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(ROOT, "_build")
 LIB = os.path.join(HERE, "libtp.so")
 SOURCES = ["api.cpp", "rollout.hip", "rollout_rs.hip", "rollout_rs_i4.hip", "rollout_rs_i10.hip",
-           "rollout_rs_i10_wide.hip", "critic.hip", "metrics.hip", "evolution.hip", "learner.hip",
+           "rollout_rs_i10_wide.hip", "rollout_four.hip", "rollout_four_n8.hip",
+           "rollout_four_bf16.hip", "rollout_four_bf16_n8.hip",
+           "critic.hip", "metrics.hip", "evolution.hip", "learner.hip",
            "env_kernels.hip", "gae.hip", "pack.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -249,6 +249,7 @@ bool packed_layout(const tp_actor *a, PackedLayout *L)
     const int ins[3] = {K1, L->H1, L->H2};
     const int outs[3] = {L->H1, L->H2, L->n};
     size_t off = 0;
+    L->four = a->dtype == TP_F32 && L->H1 <= 1024 && L->H2 <= 1024;
     for (int l = 0; l < 3; ++l) {
         size_t wbytes;
         if (a->dtype == TP_BF16) {
@@ -257,6 +258,10 @@ bool packed_layout(const tp_actor *a, PackedLayout *L)
             if (l == 2) L->NT[l] = (L->NT[l] + 3) / 4 * 4;
             L->KS[l] = ins[l] / 32;
             wbytes = (size_t)L->NT[l] * L->KS[l] * 64 * 16;
+        } else if (L->four) {
+            L->NT[l] = (outs[l] + 15) / 16;
+            L->KS[l] = (ins[l] + 15) / 16;
+            wbytes = (size_t)L->NT[l] * L->KS[l] * 1024;
         } else {
             L->NT[l] = outs[l];
             L->KS[l] = ins[l] / 4;

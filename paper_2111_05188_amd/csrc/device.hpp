@@ -51,9 +51,12 @@ __device__ __forceinline__ void box_muller(float u0, float u1, float &z0,
                                            float &z1)
 {
     const float rad = sqrtf(-2.0f * logf(u0));
-    const float ang = 6.28318530717958647692f * u1;
-    z0 = rad * cosf(ang);
-    z1 = rad * sinf(ang);
+    // the angle in half turns: exact, where a product with 2 pi would round,
+    // and without the reduction of large arguments
+    float s, c;
+    sincospif(2.0f * u1, &s, &c);
+    z0 = rad * c;
+    z1 = rad * s;
 }
 
 // The same with the hardware transcendentals: v_log_f32 (log2), v_sqrt_f32,

@@ -1,6 +1,7 @@
 // The stock-trading env step (paper Section 3, eqs. (2)-(4)) on one 16-lane
 // DPP row: a 64-lane wavefront steps four envs at once, env r on lanes
-// 16r .. 16r+15.  Lane s of a row holds stocks 8s .. 8s+7 (n <= 128), so
+// 16r .. 16r+15.  Lane s of a row holds N consecutive stocks from N s on
+// (N = 8: n <= 128; 4: n <= 64; 2: n <= 32), so
 // stock order equals (lane, slot) order and a row's lane-order prefix sum is
 // a prefix sum in stock index order.  Every cross-lane step stays inside a
 // row (row_shr scans, quad_perm / mirror butterflies), so the four envs share
@@ -25,7 +26,7 @@
 namespace tpk {
 
 constexpr int RL = 16;    // lanes per env (one DPP row)
-constexpr int SPR = 8;    // stocks per lane
+constexpr int SPR = 8;    // stocks per lane (8 by default; 2 or 4 for smaller markets)
 
 // DPP lane moves of a 64-bit value within 16-lane rows.  Lanes without a
 // source (row_shr past the row start) receive 0.
@@ -91,13 +92,15 @@ __device__ __forceinline__ int row_any_below(int x)
     return dpp32i<0x111>(v);   // exclusive: shift the inclusive OR by one lane
 }
 
-// Per-env state held by the owning row: lane s keeps stocks 8s .. 8s+7.
-struct RowEnv {
+// Per-env state held by the owning row: lane s keeps stocks N s .. N s + N-1.
+template <int N>
+struct RowEnvN {
     double cash;      // balance (same on every lane of the row)
     double value;     // total asset b + p^T h at the current row
-    int h[SPR];       // holdings (0 for stocks >= n)
-    double pd[SPR];   // prices at the current row (0 for stocks >= n)
+    int h[N];         // holdings (0 for stocks >= n)
+    double pd[N];     // prices at the current row (0 for stocks >= n)
 };
+typedef RowEnvN<SPR> RowEnv;
 
 // k = trunc(clip(a, -1, 1) * hmax), NaN -> 0 (the fp32 product truncated
 // toward zero).
@@ -112,20 +115,21 @@ __device__ __forceinline__ int row_shares_from_action(float a, float hmaxf)
 // this lane's stocks (0 for stocks >= n and for rows not stepped, which then
 // trade nothing); qd[c]: their prices at the next row.  Returns the reward
 // (same on every lane of the row).  All 64 lanes call it.
-__device__ __forceinline__ float env_step_row(const EnvConst &C, RowEnv &s, const float (&a)[SPR],
-                                              const double (&qd)[SPR])
+template <int N>
+__device__ __forceinline__ float env_step_row(const EnvConst &C, RowEnvN<N> &s, const float (&a)[N],
+                                              const double (&qd)[N])
 {
     const double fb = C.f_b;
     const float hmaxf = (float)C.hmax;
-    int k[SPR];
+    int k[N];
 #pragma unroll
-    for (int c = 0; c < SPR; ++c) k[c] = row_shares_from_action(a[c], hmaxf);
+    for (int c = 0; c < N; ++c) k[c] = row_shares_from_action(a[c], hmaxf);
 
     // sells (all exact in fp64)
-    int h[SPR];
+    int h[N];
     double sv = 0.0;
 #pragma unroll
-    for (int c = 0; c < SPR; ++c) {
+    for (int c = 0; c < N; ++c) {
         const int sc = min(max(-k[c], 0), s.h[c]);
         h[c] = s.h[c] - sc;
         sv = fma(s.pd[c], (double)sc, sv);
@@ -145,7 +149,7 @@ __device__ __forceinline__ float env_step_row(const EnvConst &C, RowEnv &s, cons
     // pending stock that can still pay for one share and buys its largest
     // affordable q <= k.  Every purchase so far is of a lower-index stock, so
     // a stock skipped as unaffordable sees the G the serial greedy would give
-    // it.  Pending stocks as an 8-bit mask per lane (bit c = stock 8s + c).
+    // it.  Pending stocks as an N-bit mask per lane (bit c = stock N s + c).
     //
     // largest q in [lo, hi] with f_b (g + p q) <= b_s, the answer known to
     // lie in [lo, hi]: an fp32 estimate of (b_s - f_b g) / (f_b p) (off by at
@@ -161,10 +165,10 @@ __device__ __forceinline__ float env_step_row(const EnvConst &C, RowEnv &s, cons
         return qq;
     };
 
-    double costp[SPR], pre[SPR], acc = 0.0;
+    double costp[N], pre[N], acc = 0.0;
     int pm = 0;
 #pragma unroll
-    for (int c = 0; c < SPR; ++c) {
+    for (int c = 0; c < N; ++c) {
         const bool pend = k[c] > 0 && fma(fb, s.pd[c], -b_s) <= 0.0;
         costp[c] = pend ? s.pd[c] * (double)k[c] : 0.0;
         pm |= pend ? 1 << c : 0;
@@ -177,17 +181,17 @@ __device__ __forceinline__ float env_step_row(const EnvConst &C, RowEnv &s, cons
         const double base = row_inclusive_scan(acc) - acc;
         int bad = 0;   // pending stocks whose prefix no longer fits
 #pragma unroll
-        for (int c = 0; c < SPR; ++c) bad |= fma(fb, base + pre[c], -b_s) > 0.0 ? 1 << c : 0;
+        for (int c = 0; c < N; ++c) bad |= fma(fb, base + pre[c], -b_s) > 0.0 ? 1 << c : 0;
         bad &= pm;
         const int below = row_any_below(bad);
         const bool after = below != 0;          // a lower lane holds the misfit
         const bool at = !after && bad != 0;     // this lane holds it
-        const int cf = __builtin_ctz(bad | 0x100);    // its stock on this lane
+        const int cf = __builtin_ctz(bad | 1 << N);    // its stock on this lane
         const int full = after ? 0 : (at ? pm & ((1 << cf) - 1) : pm);
         double gl = 0.0, gf = 0.0, pf = 0.0;
         int kf = 0;
 #pragma unroll
-        for (int c = 0; c < SPR; ++c) {
+        for (int c = 0; c < N; ++c) {
             const bool fc = (full >> c) & 1;
             h[c] += fc ? k[c] : 0;
             gl += fc ? costp[c] : 0.0;
@@ -201,7 +205,7 @@ __device__ __forceinline__ float env_step_row(const EnvConst &C, RowEnv &s, cons
         const int qf = largest_q(gf, pf, 0, kf > 0 ? kf - 1 : 0);
         if (at) {
 #pragma unroll
-            for (int c = 0; c < SPR; ++c) h[c] += c == cf ? qf : 0;
+            for (int c = 0; c < N; ++c) h[c] += c == cf ? qf : 0;
             gl += pf * (double)qf;
         }
         pm &= ~full & ~(at ? 1 << cf : 0);
@@ -211,7 +215,7 @@ __device__ __forceinline__ float env_step_row(const EnvConst &C, RowEnv &s, cons
         for (;;) {
             int aff = 0;
 #pragma unroll
-            for (int c = 0; c < SPR; ++c) aff |= fma(fb, G + s.pd[c], -b_s) <= 0.0 ? 1 << c : 0;
+            for (int c = 0; c < N; ++c) aff |= fma(fb, G + s.pd[c], -b_s) <= 0.0 ? 1 << c : 0;
             aff &= pm;
             pm = aff;
             if (__ballot(aff != 0) == 0) break;
@@ -219,11 +223,11 @@ __device__ __forceinline__ float env_step_row(const EnvConst &C, RowEnv &s, cons
             // behind a per-lane condition)
             const int below = row_any_below(aff);
             const bool hit = aff != 0 && below == 0;
-            const int ct = __builtin_ctz(aff | 0x100);
+            const int ct = __builtin_ctz(aff | 1 << N);
             double pt = 0.0;
             int kt = 1;
 #pragma unroll
-            for (int c = 0; c < SPR; ++c) {
+            for (int c = 0; c < N; ++c) {
                 const bool sel = c == ct;
                 pt = sel ? s.pd[c] : pt;
                 kt = sel ? k[c] : kt;
@@ -232,7 +236,7 @@ __device__ __forceinline__ float env_step_row(const EnvConst &C, RowEnv &s, cons
             double dg = 0.0;
             if (hit) {
 #pragma unroll
-                for (int c = 0; c < SPR; ++c) h[c] += c == ct ? qt : 0;
+                for (int c = 0; c < N; ++c) h[c] += c == ct ? qt : 0;
                 pm &= ~(1 << ct);
                 dg = pt * (double)qt;
             }
@@ -244,13 +248,13 @@ __device__ __forceinline__ float env_step_row(const EnvConst &C, RowEnv &s, cons
 
     double hv1 = 0.0;
 #pragma unroll
-    for (int c = 0; c < SPR; ++c) hv1 = fma((double)h[c], qd[c], hv1);
+    for (int c = 0; c < N; ++c) hv1 = fma((double)h[c], qd[c], hv1);
     const double V1 = nb + row_sum(hv1);
     const float r = (float)(C.reward_scale * (V1 - s.value));
     s.cash = nb;
     s.value = V1;
 #pragma unroll
-    for (int c = 0; c < SPR; ++c) {
+    for (int c = 0; c < N; ++c) {
         s.h[c] = h[c];
         s.pd[c] = qd[c];
     }

@@ -31,9 +31,13 @@ struct EnvConst {
 //        block (tile t, k-step s) holds W[16t + l%16][32s + 8(l/16) + 0..7].
 //  f32 : W_l as k-blocked transposes, [in_pad/4][out][4]: entry
 //        (k4, o, e) = W[o][4 k4 + e].
-//  Biases fp32 [out padded to whole tiles]; log_std fp32 [NT3 * 16].
+//  four: (fp32 up to 1,024 wide) W_l as fragments [NT][KS][64 lanes][4 fp32]:
+//        lane l of tile t, k-step s holds W[16t + l%16][16s + 4(l/16) + 0..3].
+//  Biases fp32 [out, bf16: padded to whole tiles]; log_std fp32 [n, bf16: NT3
+//  * 16].
 struct PackedLayout {
     int dtype;
+    bool four;
     int S, H1, H2, n;
     int K_pad;
     int NT[3];            // output tiles of 16 (bf16)
@@ -76,6 +80,8 @@ struct RolloutArgs {
 
 hipError_t launch_rollout(RolloutArgs &a, hipStream_t s);
 hipError_t launch_rollout_rs(RolloutArgs &a, hipStream_t s);
+// the four-env kernel: hidden widths to 1,024, fp32 packed as `four`
+hipError_t launch_rollout_four(RolloutArgs &a, hipStream_t s);
 // the role-split kernel's shapes (it also needs 16-byte aligned market,
 // action and holdings-tap buffers)
 bool rollout_rs_shape(const PackedLayout &P, int nI);

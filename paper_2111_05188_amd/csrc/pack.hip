@@ -37,6 +37,23 @@ __global__ void pack_f32_kernel(const float *__restrict__ W, int out, int in,
     }
 }
 
+// fp32 MFMA fragments: element (t, b, lane, e) of [NT][KB][64][4] is
+// W[16t + lane%16][16b + 4(lane/16) + e], zero outside [out][in].
+__global__ void pack_frag_f32_kernel(const float *__restrict__ W, int out, int in, int NT, int KB,
+                                     float *__restrict__ dst)
+{
+    const size_t total = (size_t)NT * KB * WAVE * 4;
+    for (size_t p = blockIdx.x * (size_t)blockDim.x + threadIdx.x; p < total;
+         p += (size_t)gridDim.x * blockDim.x) {
+        const int e = (int)(p % 4);
+        const int lane = (int)((p / 4) % WAVE);
+        const size_t tb = p / (4 * WAVE);
+        const int b = (int)(tb % KB), t = (int)(tb / KB);
+        const int o = 16 * t + (lane % 16), k = 16 * b + 4 * (lane / 16) + e;
+        dst[p] = (o < out && k < in) ? W[(size_t)o * in + k] : 0.0f;
+    }
+}
+
 // Copy `cnt` floats and zero-fill up to `padded`.
 __global__ void pack_vec_kernel(const float *__restrict__ src, int cnt,
                                 int padded, float *__restrict__ dst)
@@ -53,23 +70,6 @@ __global__ void pack_vec_bf16_kernel(const float *__restrict__ src, int cnt,
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < padded;
          i += gridDim.x * blockDim.x)
         dst[i] = i < cnt ? (float)to_bf16(src[i]) : 0.0f;
-}
-
-// fp32 MFMA fragments: element (t, b, lane, e) of [NT][KB][64][4] is
-// W[16t + lane%16][16b + 4(lane/16) + e], zero outside [out][in].
-__global__ void pack_frag_f32_kernel(const float *__restrict__ W, int out, int in, int NT, int KB,
-                                     float *__restrict__ dst)
-{
-    const size_t total = (size_t)NT * KB * WAVE * 4;
-    for (size_t p = blockIdx.x * (size_t)blockDim.x + threadIdx.x; p < total;
-         p += (size_t)gridDim.x * blockDim.x) {
-        const int e = (int)(p % 4);
-        const int lane = (int)((p / 4) % WAVE);
-        const size_t tb = p / (4 * WAVE);
-        const int b = (int)(tb % KB), t = (int)(tb / KB);
-        const int o = 16 * t + (lane % 16), k = 16 * b + 4 * (lane / 16) + e;
-        dst[p] = (o < out && k < in) ? W[(size_t)o * in + k] : 0.0f;
-    }
 }
 
 static int grid_for(size_t total)
@@ -132,7 +132,11 @@ hipError_t launch_pack(const tp_actor *a, const PackedLayout &L, void *dst,
         for (int l = 0; l < 3; ++l) {
             const float *W = a->W[l] + (size_t)ag * (a->agent_stride ? (size_t)a->agent_stride
                                                                      : (size_t)outs[l] * ins[l]);
-            if (L.dtype == TP_BF16) {
+            if (L.four) {
+                const size_t tot = (size_t)L.NT[l] * L.KS[l] * WAVE * 4;
+                hipLaunchKernelGGL(pack_frag_f32_kernel, dim3(grid_for(tot)), dim3(256), 0, s, W,
+                                   outs[l], ins[l], L.NT[l], L.KS[l], (float *)(pa + L.off_W[l]));
+            } else if (L.dtype == TP_BF16) {
                 const size_t tot = (size_t)L.NT[l] * L.KS[l] * WAVE * 8;
                 const int grid = (int)((tot + 255) / 256 < 4096 ? (tot + 255) / 256 : 4096);
                 hipLaunchKernelGGL(pack_bf16_kernel, dim3(grid), dim3(256), 0, s, W, outs[l],

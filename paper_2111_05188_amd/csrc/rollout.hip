@@ -1,4 +1,6 @@
-// Fused rollout kernel: L lockstep steps of a block of envs in one launch.
+// Generic fused rollout kernel: L lockstep steps of a block of envs in one
+// launch, for the shapes that neither the role-split kernel (rollout_rs.hpp)
+// nor the four-env kernel (rollout_four.hpp) takes, and the dispatch.
 //
 // A workgroup owns MB envs of one agent for the whole rollout (envs are
 // independent, so workgroups never synchronise with each other).  Per step:
@@ -107,14 +109,12 @@ __device__ __forceinline__ void mfma_layer(const bf16x8 *__restrict__ W,
     }
 }
 
-// fp32 VALU layer: thread o computes output o for all MB envs; weights are
-// k-blocked transposes so consecutive threads read consecutive 16 bytes.
-// A layer with at most half as many outputs as threads (the action means)
-// gives each output T consecutive lanes (T the largest power of two with
-// out * T <= nthr, at most 64) that split its k-blocks and combine by xor
-// shuffles in a fixed order: 10% faster on the 30-stock daily shape, where
-// 30 threads would otherwise walk 64 k-blocks each.  Deeper unrolling of
-// the k loop measured slower.
+// fp32 VALU layer (hidden layers wider than 1,024): thread o computes output o
+// for all MB envs; weights are k-blocked transposes so consecutive threads
+// read consecutive 16 bytes.  A layer with at most half as many outputs as
+// threads (the action means) gives each output T consecutive lanes (T the
+// largest power of two with out * T <= nthr, at most 64) that split its
+// k-blocks and combine by xor shuffles in a fixed order.
 template <int MB, bool HIDDEN>
 __device__ __forceinline__ void valu_layer(const float4 *__restrict__ Wt,
                                            const float *__restrict__ bias,
@@ -478,9 +478,21 @@ hipError_t launch_rollout(RolloutArgs &a, hipStream_t s)
         const hipError_t e = launch_zero_i32(a.n_invalid, s);
         if (e != hipSuccess) return e;
     }
+    if (a.lay.four) return launch_rollout_four(a, s);
     if (a.lay.dtype == TP_BF16) {
         const hipError_t e = launch_rollout_rs(a, s);
         if (e != hipErrorNotSupported) return e;
+        // The four-env kernel, but for wide actors of many envs: it streams
+        // the weights a CU cannot keep once per 8 envs, the generic kernel
+        // once per 16.  With 1001-512-384-100 a step of 512 envs takes 17 us
+        // against 23, of 4,096 (two rounds of workgroups of 8 envs on the
+        // 256 CUs) 45 against 24; with 301-256-256-30 nearly all weights stay,
+        // and a step of 1,332 envs takes 5.1 us against 13.
+        const PackedLayout &P = a.lay;
+        const int64_t rounds = ((int64_t)a.n_agents * ((a.envs_per_agent + 7) / 8) + 255) / 256;
+        const int64_t weights = ((int64_t)P.S * P.H1 + (int64_t)P.H1 * P.H2 + (int64_t)P.H2 * P.n) * 2;
+        if (P.H1 <= 1024 && P.H2 <= 1024 && (rounds == 1 || weights <= 400 * 1024))
+            return launch_rollout_four(a, s);
         const int *k = a.lay.KS;
         // fully unrolled variants for the actor shapes in use
         if (k[0] == 32 && k[1] == 16 && k[2] == 16) return launch_cfg<__bf16, 2, 8, 32, 16, 16>(a, s);

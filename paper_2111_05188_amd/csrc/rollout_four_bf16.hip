@@ -1,0 +1,8 @@
+// Four-env rollout kernel (rollout_four.hpp): bf16 actors of up to 32 stocks.
+#include "rollout_four.hpp"
+
+namespace tpk {
+namespace four {
+template hipError_t launch_type<true, 2>(RolloutArgs &, hipStream_t);
+}  // namespace four
+}  // namespace tpk

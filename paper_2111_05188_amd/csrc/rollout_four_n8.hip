@@ -1,0 +1,8 @@
+// Four-env rollout kernel (rollout_four.hpp): fp32 actors of more than 32 stocks.
+#include "rollout_four.hpp"
+
+namespace tpk {
+namespace four {
+template hipError_t launch_type<false, 8>(RolloutArgs &, hipStream_t);
+}  // namespace four
+}  // namespace tpk

@@ -1,8 +1,8 @@
 """GPU parity of tp_rollout (fused actor + sampling + env step + trajectory
 store) against a teacher-forced oracle replay, at sizes the oracle finishes
 in seconds: several workgroups of envs, ragged tails, every actor shape
-family (fp32 VALU, bf16 MFMA 256- to 1024-wide on the role-split kernel,
-bf16 of another shape on the generic kernel, multi-agent), plus
+family (bf16 256- to 1024-wide on the role-split kernel, fp32 and other bf16
+shapes on the four-env kernel, the rest on the generic kernel, multi-agent), plus
 determinism, split/resume, and envs whose start row leaves no room."""
 
 import numpy as np
@@ -112,23 +112,43 @@ def test_dow_shape_small():
 
 
 def test_bf16_actor_of_another_shape():
-    # a bf16 actor outside the shapes with a specialised kernel (301 inputs,
-    # 256-wide layers) runs the generic MFMA rollout kernel
+    # a bf16 actor outside the role-split kernel's shapes (301 inputs, 256-wide
+    # layers) runs the four-env kernel
     _run_case(W.get_config("dow30").with_(dtype="bf16"), 21, 120, rows=2521)
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_largest_market(dtype):
     # 128 stocks x 8 indicators (n * n_ind = 1024, the largest market the
-    # boundary takes; 1281 inputs) on the generic kernel, fp32 and bf16
+    # boundary takes; 1281 inputs) on the four-env kernel, fp32 and bf16
     cfg = W.get_config("tiny").with_(n=128, n_ind=8, dtype=dtype, hidden=(128, 128))
     pb = _run_case(cfg, 20, 40)
     assert tp.rollout_path(pb.mkt, pb.actor) == 0
 
 
+@pytest.mark.parametrize("n,I,hidden,E,L,agents,dtype", [
+    (1, 0, (4, 4), 1, 1, 1, "f32"),          # one stock, no indicators, one k-block
+    (8, 8, (16, 16), 5, 2, 1, "f32"),        # holdings end on a k-block's edge
+    (5, 4, (96, 36), 1030, 3, 1, "f32"),     # eight envs a workgroup, a ragged last one
+    (33, 8, (320, 192), 9, 4, 3, "f32"),     # eight stocks a lane, two tile groups of layer 1
+    (20, 8, (1024, 500), 6, 3, 1, "f32"),    # four groups; layers that stream
+    (5, 4, (1028, 64), 6, 3, 1, "f32"),      # wider than the kernel: the generic one
+    (31, 3, (256, 128), 1100, 3, 2, "bf16"),
+    (64, 4, (128, 384), 21, 2, 3, "bf16"),
+    (128, 8, (640, 128), 7, 3, 1, "bf16"),
+    (100, 5, (256, 384), 2064, 2, 1, "bf16"),    # many envs of a wide actor: the generic kernel
+])
+def test_four_env_kernel_edges(n, I, hidden, E, L, agents, dtype):
+    cfg = W.get_config("tiny").with_(name=f"four-{n}", n=n, n_ind=I, hidden=hidden, dtype=dtype)
+    ids = None if E < 100 else np.r_[0:5, E // agents - 3:E // agents + 3, E - 9:E]
+    ids = ids if ids is None else np.unique(ids[ids < E])
+    pb = _run_case(cfg, E, L, rows=8, n_agents=agents, cmp_ids=ids)
+    assert tp.rollout_path(pb.mkt, pb.actor) == 0
+
+
 def test_bf16_100_stock_actor_outside_the_role_split_shapes():
-    # unequal hidden widths (512-256) on the 100 x 8 market: the generic
-    # MFMA kernel takes it, with the same results contract
+    # unequal hidden widths (512-256) on the 100 x 8 market: the four-env
+    # kernel takes it, with the same results contract
     cfg = W.get_config("nasdaq100").with_(hidden=(512, 256))
     pb = _run_case(cfg, 21, 30, rows=20 * 390 + 1)
     assert tp.rollout_path(pb.mkt, pb.actor) == 0
