@@ -98,6 +98,12 @@ def test_critic_mfma_three_agents():
     _run(W.get_config("ensemble"), 135, 5, n_agents=3)
 
 
+@pytest.mark.parametrize("name", ["nasdaq100", "stress"])
+def test_critic_mfma_few_envs_per_agent(name):
+    # two envs an agent: a block of rows spans 32 or 64 steps, the last one ragged
+    _run(W.get_config(name), 6, 70, n_agents=3)
+
+
 def test_critic_generic_fp32():
     _run(W.get_config("tiny"), 40, 30)
     _run(W.get_config("dow30"), 33, 20)
