@@ -387,6 +387,15 @@ constexpr int LBK = 128;              // k per chunk
 constexpr int LROW = LBK + GEMM_LPAD; // padded LDS row (bf16)
 constexpr int LTILE = GT * LROW;      // one operand's chunk (bf16)
 
+// Launches with another K than lds_kloop's 128, 512 and 1024 come here when
+// one learner has this many 64 x 64 tiles (the number of learners plays no
+// part, so a learner's sums keep their order in any group of them).  Below
+// it, gemm_split_kernel's 32 x 32 tiles fill the chip better.  An update of
+// one learner, gemm_split_kernel -> this kernel: 512 x 512, 2,048 rows 473 ->
+// 427 us; 768 x 768, 1,248 rows 510 -> 465; 640 x 640, 640 rows 351 -> 325.
+// With the line at 128 instead: 384 x 384, 704 rows 222 -> 228, and 256 x 256,
+// 1,024 rows 231 -> 239.
+constexpr int LDS_MIN_TILES = 200;
 typedef uint32_t v4u_t __attribute__((ext_vector_type(4)));
 
 constexpr int LWAVES = 8;              // waves per workgroup: 2 (rows) x 4 (columns)
@@ -569,6 +578,76 @@ __device__ __forceinline__ void lds_kloop(const __bf16 *const ga, const __bf16 *
     });
 }
 
+// The same for any K that is a multiple of 32 (zeros past K in the last
+// chunk): chunks in pairs, so that each register set keeps its place.
+__device__ __forceinline__ void lds_kloop_any(const __bf16 *const ga, const __bf16 *const gb,
+                                              int64_t lda, int64_t ldb, int Mr, int Nr, int K,
+                                              __bf16 *smem, floatx4 acc[2])
+{
+    const int tid = threadIdx.x, lane = tid % WAVE, wave = tid / WAVE;
+    const int r16 = lane & 15, kq = lane >> 4;
+    const int lrow = tid >> 4, lpiece = tid & 15;
+    const __bf16 *la[2], *lb[2];
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+        la[j] = ga + (size_t)min(lrow + 32 * j, Mr - 1) * lda + lpiece * 8;
+        lb[j] = gb + (size_t)min(lrow + 32 * j, Nr - 1) * ldb + lpiece * 8;
+    }
+    const int nc = (K + LBK - 1) / LBK;
+    v4u_t ra[2][2], rb[2][2];
+    auto load = [&](auto sc, int c) {
+        constexpr int S = decltype(sc)::value;
+        const bool in = c * LBK + lpiece * 8 < K;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            ra[S][j] = in ? *(const v4u_t *)(la[j] + c * LBK) : v4u_t{0, 0, 0, 0};
+            rb[S][j] = in ? *(const v4u_t *)(lb[j] + c * LBK) : v4u_t{0, 0, 0, 0};
+        }
+    };
+    auto store = [&](auto sc, int buf) {
+        constexpr int S = decltype(sc)::value;
+        __bf16 *As = smem + buf * 2 * LTILE, *Bs = As + LTILE;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            *(v4u_t *)(As + (lrow + 32 * j) * LROW + lpiece * 8) = ra[S][j];
+            *(v4u_t *)(Bs + (lrow + 32 * j) * LROW + lpiece * 8) = rb[S][j];
+        }
+    };
+    load(ic<0>{}, 0);
+    if (nc > 1) load(ic<1>{}, 1);
+    store(ic<0>{}, 0);
+    if (nc > 2) load(ic<0>{}, 2);
+    __syncthreads();
+    const int am = (wave >> 2) * 32, bn = (wave & 3) * 16;
+    // chunk c (LDS buffer B = c & 1): chunk c + 1 sits in register set 1 - B
+    auto chunk = [&](auto bc, int c) {
+        constexpr int B = decltype(bc)::value;
+        const __bf16 *As = smem + B * 2 * LTILE, *Bs = As + LTILE;
+        bf16x8 fa[LBK / 32][2], fb[LBK / 32];
+#pragma unroll
+        for (int q = 0; q < LBK / 32; ++q) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                fa[q][i] = *(const bf16x8 *)(As + (am + i * 16 + r16) * LROW + q * 32 + kq * 8);
+            fb[q] = *(const bf16x8 *)(Bs + (bn + r16) * LROW + q * 32 + kq * 8);
+        }
+        if (c + 1 < nc) {
+            store(ic<1 - B>{}, 1 - B);
+            if (c + 3 < nc) load(ic<1 - B>{}, c + 3);
+        }
+#pragma unroll
+        for (int q = 0; q < LBK / 32; ++q)
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+                acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[q][i], fb[q], acc[i], 0, 0, 0);
+        if (c + 1 < nc) __syncthreads();
+    };
+    for (int c = 0; c < nc; c += 2) {
+        chunk(ic<0>{}, c);
+        if (c + 1 < nc) chunk(ic<1>{}, c + 1);
+    }
+}
+
 __global__ __launch_bounds__(LTHREADS, 2) void gemm_lds_kernel(GemmBatch gb)
 {
     __shared__ __attribute__((aligned(16))) __bf16 smem[2 * 2 * LTILE];
@@ -588,11 +667,11 @@ __global__ __launch_bounds__(LTHREADS, 2) void gemm_lds_kernel(GemmBatch gb)
 #pragma unroll
     for (int i = 0; i < 2; ++i) acc[i] = floatx4{0.f, 0.f, 0.f, 0.f};
     const int Mr = P.M - m0, Nr = P.N - n0;     // rows left in this tile (>= 1)
-    switch (P.K / LBK) {
+    switch (P.K % LBK == 0 ? P.K / LBK : 0) {
     case 1: lds_kloop<1>(ga, gbp, P.lda, P.ldb, Mr, Nr, smem, acc); break;
     case 4: lds_kloop<4>(ga, gbp, P.lda, P.ldb, Mr, Nr, smem, acc); break;
     case 8: lds_kloop<8>(ga, gbp, P.lda, P.ldb, Mr, Nr, smem, acc); break;
-    default: break;   // the launcher routes other K to gemm_split_kernel
+    default: lds_kloop_any(ga, gbp, P.lda, P.ldb, Mr, Nr, P.K, smem, acc); break;
     }
     const int wm = m0 + (wave >> 2) * 32, wn = n0 + (wave & 3) * 16;
     if (P.mode == EPI_BIAS) {
@@ -1473,19 +1552,22 @@ hipError_t run_gemms(bool bf, const Agents &ag, std::initializer_list<GemmProb> 
     GemmBatch gb{};
     gb.aws = ag.aws;
     gb.aprm = ag.aprm;
-    // kernel choice: bf16 products with K in {128, 512, 1024} go through
-    // LDS, in 256 x 128 tiles when the launch has at least BIG_MIN_TILES
-    // tiles' worth of 128 x 128
-    bool staged = bf, big = bf;
-    int tiles_big = 0;
+    // kernel choice: bf16 products with K in {128, 512, 1024}, and others with
+    // LDS_MIN_TILES tiles, go through LDS; the former in 256 x 128 tiles when
+    // the launch has at least BIG_MIN_TILES tiles' worth of 128 x 128
+    bool staged = bf, big = bf, fixed = true;
+    int tiles_big = 0, tiles_lds = 0;
     for (const GemmProb &p : ps) {
-        const int nc = p.K / LBK, nb = p.K / BBK;
+        const int nb = p.K / BBK;
         const bool ld_ok = p.lda % 8 == 0 && p.ldb % 8 == 0;
-        staged = staged && p.K % LBK == 0 && (nc == 1 || nc == 4 || nc == 8) && ld_ok;
+        staged = staged && ld_ok;
+        fixed = fixed && p.K % LBK == 0 && (p.K / LBK == 1 || p.K / LBK == 4 || p.K / LBK == 8);
+        tiles_lds += cdiv(p.M, GT) * cdiv(p.N, GT);
         big = big && p.K % BBK == 0 && (nb == 2 || nb == 8 || nb == 16) && ld_ok;
         tiles_big += cdiv(p.M, BT) * cdiv(p.N, BT);
     }
     big = big && tiles_big * ag.n >= BIG_MIN_TILES;
+    staged = staged && (fixed || tiles_lds >= LDS_MIN_TILES);
     const int TN = big ? BT : staged ? GT : ST, TM = big ? BM : staged ? GT : ST;
     int tiles = 0;
     for (const GemmProb &p : ps) {

@@ -404,3 +404,28 @@ def test_products_split_over_the_waves(n, hidden, B, dtype):
     cfg = W.get_config("tiny").with_(name=f"split-{n}", n=n, hidden=hidden, dtype=dtype)
     r = _run(cfg, 2 * B, B, 1)
     _check_grad(r["dims"], r["grad"], r["g_o"], GRAD_TOL[dtype], f"{n} {hidden} {B} {dtype}")
+
+
+@pytest.mark.parametrize("n,hidden,B", [
+    (9, (1056, 1056), 416),   # K = 1056 (a quarter chunk last), 416, 64 inputs; ragged tiles
+    (33, (672, 608), 1312),   # K = 1312, 672, 608: an odd chunk last, actions past 32
+    (3, (32, 32), 6400),      # 200 row tiles of one 32-input chunk (no pair, half a tile)
+    (100, (512, 512), 2048),  # K = 2048: whole chunks of another count, 576-column inputs
+])
+def test_products_through_lds_any_k(n, hidden, B):
+    """bf16 products with many tiles and another K than the unrolled ones,
+    against the oracle's gradient, by each segment's relative L2 error.
+
+    Bound: a gradient passes through four matrices that are rounded to bf16
+    (two activations, two back-propagated signals), each of which can land on
+    the other side of a rounding after sums in another order: 2^-9 of an
+    element each, 4 * 2^-9 = 2^-7 together.  A 32-deep block that is lost or
+    counted twice moves a segment by about sqrt(32 / K) >= 0.07.  (The largest
+    single element of 300,000 lies near 0.023 of its segment's RMS in any
+    order of the sums, so GRAD_TOL is for smaller networks.)"""
+    cfg = W.get_config("tiny").with_(name=f"lds-{n}", n=n, hidden=hidden, dtype="bf16")
+    r = _run(cfg, B, B, 1)
+    g, o = (ppo.unflatten(np.asarray(x, dtype=np.float64), r["dims"]) for x in (r["grad"], r["g_o"]))
+    for name, _ in ppo.layout(*r["dims"]):
+        e = _rel(np.asarray(g[name]).ravel(), np.asarray(o[name]).ravel())
+        assert e <= 2.0 ** -7, (n, hidden, B, name, e)
