@@ -179,7 +179,7 @@ def test_critic_packed_bytes_host_only():
     frag = (32 * 32 + 32 * 16) * 1024
     assert frag < nb < frag + 16 * 1024
     assert L.tp_critic_packed_bytes(C.byref(_critic(A=3))) == 3 * nb
-    # generic layout (fp32 transposes): K_pad x H1 + H1 x H2 floats
+    # fp32 fragments: K_pad x H1 + H1 x H2 floats
     nb32 = L.tp_critic_packed_bytes(C.byref(_critic(dims=(301, 256, 256), dtype=tp.TP_F32)))
     assert (320 * 256 + 256 * 256) * 4 < nb32 < (320 * 256 + 256 * 256) * 4 + 8 * 1024
     assert L.tp_critic_packed_bytes(C.byref(_critic(dims=(301, 250, 256)))) == 0
