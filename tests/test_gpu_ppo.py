@@ -394,6 +394,8 @@ def test_partial_column_blocks_in_staged_products():
     (5, (32, 32), 32, "f32"),        # K = 32: two k-blocks for four waves
     (7, (96, 224), 160, "f32"),      # ragged tiles: 43 inputs, 7 actions, odd block counts
     (33, (288, 64), 96, "f32"),      # action columns past one tile
+    (3, (32, 4128), 32, "f32"),      # a critic head wider than the loss kernel stages at a time
+    (3, (64, 2080), 32, "f32"),      # a head of many rounds, half a column tile last
     (5, (32, 32), 32, "bf16"),       # K = 32: one k-block
     (7, (96, 224), 160, "bf16"),
     (33, (288, 64), 96, "bf16"),
@@ -410,6 +412,7 @@ def test_products_split_over_the_waves(n, hidden, B, dtype):
     (9, (1056, 1056), 416),   # K = 1056 (a quarter chunk last), 416, 64 inputs; ragged tiles
     (33, (672, 608), 1312),   # K = 1312, 672, 608: an odd chunk last, actions past 32
     (3, (32, 32), 6400),      # 200 row tiles of one 32-input chunk (no pair, half a tile)
+    (3, (32, 4128), 32),      # a critic head wider than the loss kernel stages at a time
     (100, (512, 512), 2048),  # K = 2048: whole chunks of another count, 576-column inputs
 ])
 def test_products_through_lds_any_k(n, hidden, B):
