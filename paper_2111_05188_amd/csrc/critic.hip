@@ -386,7 +386,10 @@ __device__ __forceinline__ void tile_layer(const uint8_t *W, const float *bias, 
             for (int r = 0; r < RT; ++r) {
                 e4 h;
 #pragma unroll
-                for (int e = 0; e < 4; ++e) h[e] = (E)tanh_f32(acc[t][r][e] + bv[e]);
+                for (int e = 0; e < 4; ++e) {
+                    const float z = acc[t][r][e] + bv[e];
+                    h[e] = (E)(BF ? tanh_for_bf16<true>(z) : tanh_f32<true>(z));
+                }
                 if (LAST) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) part[r] = fmaf(wv[e], (float)h[e], part[r]);

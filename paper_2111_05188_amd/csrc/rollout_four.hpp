@@ -279,7 +279,7 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
             for (int t = 0; t < G; ++t)
 #pragma unroll
                 for (int g = 0; g < NG; ++g)
-                    v[t][g] = BF ? tanh_from_e2(NEG_2LOG2E * v[t][g]) : tanh_f32(v[t][g]);
+                    v[t][g] = BF ? tanh_for_bf16(v[t][g]) : tanh_f32(v[t][g]);
         }
 #pragma unroll
         for (int t = 0; t < G; ++t)

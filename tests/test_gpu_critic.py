@@ -147,3 +147,40 @@ def test_critic_full_nasdaq_trajectory_sampled():
     tp.critic_value(crit, obs_all, values)
     torch.cuda.synchronize()
     assert torch.equal(v0, values)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_tanh_of_the_tile_kernel(dtype):
+    """The hidden layers' tanh, read through a critic that passes one input
+    on: h1 = tanh(x), then a second layer whose input is scaled by 2^-20 (its
+    tanh is its argument, to 2^-40) and a head of 2^20, so V = tanh(x).
+
+    fp32: within 1 ulp of tanh (measured over every fp32 value: 0.975; the
+    library's tanhf reaches 1.41).  bf16: half a bf16 ulp and what the fp32
+    error before the rounding adds, 1.35 * 2^-16 of one."""
+    k = torch.arange(2 ** 20, dtype=torch.float64, device="cuda")
+    x = torch.cat([12.0 * (k + 0.5) / 2 ** 20, 2.0 ** (-40 + 40 * k / 2 ** 20),
+                   torch.tensor([0.0, 1.0, 10.0, 1e30], dtype=torch.float64, device="cuda")])
+    x = torch.cat([x, -x]).float()
+    bf = dtype == "bf16"
+    if bf:
+        x = x.bfloat16().float()
+    W1, W2, w3 = torch.zeros(1, 4, 1), torch.zeros(1, 4, 4), torch.zeros(1, 4)
+    W1[0, 0, 0], W2[0, 0, 0], w3[0, 0] = 1.0, 2.0 ** -20, 2.0 ** 20
+    b = [torch.zeros(1, 4).cuda(), torch.zeros(1, 4).cuda(), torch.zeros(1).cuda()]
+    crit = tp.CriticT([W1.cuda(), W2.cuda(), w3.cuda()], b, (1, 4, 4),
+                      tp.TP_BF16 if bf else tp.TP_F32, 1024)
+    crit.pack()
+    T = -(-x.numel() // 1024)
+    rows = torch.zeros(T * 1024, 32, device="cuda")
+    rows[:x.numel(), 0] = x
+    rows = rows.view(T, 1024, 32)
+    value = torch.empty(T, 1024, device="cuda")
+    say(f"[critic] tanh {dtype}")
+    tp.critic_value(crit, rows.bfloat16() if bf else rows, value)
+    torch.cuda.synchronize()
+    got, want = value.view(-1)[:x.numel()].double(), torch.tanh(x.double())
+    ulp = torch.exp2(torch.floor(torch.log2(want.abs().clamp(min=2.0 ** -126))) - (7 if bf else 23))
+    err = ((got - want).abs() / ulp).max().item()
+    say(f"    worst error {err:.4f} ulp of {dtype}")
+    assert err <= (0.5 + 1.35 * 2.0 ** -16 if bf else 1.0)
