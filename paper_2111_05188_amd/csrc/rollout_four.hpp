@@ -124,15 +124,23 @@ __device__ __forceinline__ void mma(const u4v &w, const u4v &x, floatx4 &acc)
                                                  __builtin_bit_cast(floatx4, w)[E], acc, 0, 0, 0);
     }
 }
+// Accumulators of G tiles: two each for one tile at a time (narrow networks
+// and the action layer), the even and the odd elements of every lane's 16
+// bytes, so eight partial sums an output: the sums of short layers are then no
+// further from 64 bits than the VALU layers' of fp32 actors over 1,024 wide,
+// which are split over as many lanes.
+template <int G>
+constexpr int ACCS = G == 1 ? 2 : G;
+
 template <bool BF, int NG, int G>
-__device__ __forceinline__ void block(const u4v *w, const u4v *x, floatx4 (&acc)[G][NG])
+__device__ __forceinline__ void block(const u4v *w, const u4v *x, floatx4 (&acc)[ACCS<G>][NG])
 {
     auto each = [&](auto e) {
         constexpr int E = decltype(e)::value;
 #pragma unroll
         for (int t = 0; t < G; ++t)
 #pragma unroll
-            for (int g = 0; g < NG; ++g) mma<BF, E>(w[t], x[g], acc[t][g]);
+            for (int g = 0; g < NG; ++g) mma<BF, E>(w[t], x[g], acc[G == 1 ? E % 2 : t][g]);
     };
     each(ic<0>{});
     each(ic<1>{});
@@ -272,7 +280,8 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
             o[t] = min(t0 + t, q.nt - 1) * 16 + lane % 16;
             const float bo = b[o[t]];
 #pragma unroll
-            for (int g = 0; g < NG; ++g) v[t][g] = sum_kq(acc[t][g]) + bo;
+            for (int g = 0; g < NG; ++g)
+                v[t][g] = sum_kq(G == 1 ? acc[0][g] + acc[ACCS<G> - 1][g] : acc[t][g]) + bo;
         }
         if constexpr (l < 2) {
 #pragma unroll
@@ -316,7 +325,7 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
     for (int j = 0; j < A.L; ++j) {
         const uint8_t *x = x0 + (j & 1) * (MB * P.ldx);
         // slot A: market columns of layer 1
-        floatx4 z[TW][GT][NG];
+        floatx4 z[TW][ACCS<GT>][NG];
 #pragma unroll
         for (int i = 0; i < TW; ++i) {
             clear(z[i]);
@@ -344,7 +353,7 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
         __syncthreads();
         // slot L2: the first group with its registers, the others streamed
         if (has2) {
-            floatx4 acc[GT][NG];
+            floatx4 acc[ACCS<GT>][NG];
             clear(acc);
             run(g, j2, k2, h1, P.ldh1, acc);
             if (earlyA && has1) prime(g, jm, jm.kb);
@@ -367,7 +376,7 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
         }
         for (int t = t0 + MW * GT; t < P.part[2].nt; t += MW * GT) {
             const Job q = job(P.part[2], t);
-            floatx4 acc[GT][NG];
+            floatx4 acc[ACCS<GT>][NG];
             clear(acc);
             prime(g, q, q.kb);
             run(g, q, q.kb, h1, P.ldh1, acc);
@@ -379,7 +388,7 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
         // slot L3 (at most two tiles a wave)
         for (int t = w; t < P.part[3].nt; t += MW) {
             const Job q = job(P.part[3], t);
-            floatx4 acc[1][NG];
+            floatx4 acc[ACCS<1>][NG];
             clear(acc);
             if (t != w) prime(ic<1>{}, q, q.kb);
             run(ic<1>{}, q, q.kb, h2, P.ldh2, acc);
