@@ -293,3 +293,23 @@ def test_narrow_fp32_actor_against_64_bits():
     e = _rel2(pb.traj.mu_tap[0].cpu().numpy(), mu)
     say(f"    mu {e:.3e}")
     assert e <= 1.2e-7
+
+
+def test_normals_and_log_density_against_64_bits():
+    """The normals' log-density of 30 stocks: fp32 rounds the result (a relative
+    2.5e-8 in the 2-norm for values in [2^5, 2^6)) and each of the 30 normals
+    (1.5e-8 with correctly rounded ones), together 2.9e-8; a logarithm that is
+    2.6e-8 too small on average takes it to 3.5e-8."""
+    import oracle
+    pb, mu = _one_bar(30, 8, 64)
+    key = (SEED & 0xFFFFFFFF, SEED >> 32)
+    w = np.array([[oracle.philox((k, e, 0, 0), key) for k in range(8)] for e in range(1024)])
+    u = ((w.astype(np.int64) >> 9) + 0.5) * 2.0 ** -23
+    rad, ang = np.sqrt(-2 * np.log(u[..., 0::2])), 2 * np.pi * u[..., 1::2]
+    z = np.stack([rad * np.cos(ang), rad * np.sin(ang)], -1).reshape(1024, -1)[:, :30]
+    ls = float(pb.actor.log_std[0, 0])
+    logp = (-0.5 * z * z - ls).sum(1) - 15 * np.log(2 * np.pi)
+    e = _rel2(pb.traj.logp[0].cpu().numpy(), logp)
+    a = _rel2(pb.traj.action[0].cpu().numpy(), mu + np.exp(ls) * z)
+    say(f"    logp {e:.3e} action {a:.3e}")
+    assert e <= 3.0e-8 and a <= 1.1e-7
