@@ -313,7 +313,7 @@ constexpr int TILE_NW = 4;   // waves per workgroup
 // LAST one, part[rt] += w3 . h of this lane's outputs.
 template <bool BF, int RT, int NW, int OT, bool LAST>
 __device__ __forceinline__ void tile_layer(const uint8_t *W, const float *bias, const float *w3,
-                                           int NT, int KB, const uint8_t *xs, int ldx, uint8_t *hs,
+                                           int H, int NT, int KB, const uint8_t *xs, int ldx, uint8_t *hs,
                                            int ldh, float (&part)[RT], bool over, int wave, int lane)
 {
     typedef typename TileType<BF>::E E;
@@ -390,6 +390,9 @@ __device__ __forceinline__ void tile_layer(const uint8_t *W, const float *bias, 
                     const float z = acc[t][r][e] + bv[e];
                     h[e] = (E)(BF ? tanh_for_bf16<true>(z) : tanh_f32<true>(z));
                 }
+                // past the layer's outputs zeros, not what zero weights give
+                // (NaN where an input is infinite); widths are multiples of 4
+                if (o >= H) h = e4{};
                 if (LAST) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) part[r] = fmaf(wv[e], (float)h[e], part[r]);
@@ -453,12 +456,12 @@ __global__ __launch_bounds__(NW *WAVE) void critic_tile_kernel(CriticArgs A, int
     auto layer = [&](auto last, int l, const float *b, const uint8_t *x, int ld) {
         constexpr bool LAST = decltype(last)::value;
         const uint8_t *W = pk + P.off_W[l];
-        const int NT = P.NT[l], KB = P.KS[l];
+        const int H = l == 0 ? P.H1 : P.H2, NT = P.NT[l], KB = P.KS[l];
         switch (tiles_per_wave(NT, NW)) {
-        case 1: tile_layer<BF, RT, NW, 1, LAST>(W, b, w3, NT, KB, x, ld, hs, ldh, part, !LAST && over, wave, lane); break;
-        case 2: tile_layer<BF, RT, NW, 2, LAST>(W, b, w3, NT, KB, x, ld, hs, ldh, part, !LAST && over, wave, lane); break;
-        case 3: tile_layer<BF, RT, NW, 3, LAST>(W, b, w3, NT, KB, x, ld, hs, ldh, part, !LAST && over, wave, lane); break;
-        default: tile_layer<BF, RT, NW, 4, LAST>(W, b, w3, NT, KB, x, ld, hs, ldh, part, !LAST && over, wave, lane); break;
+        case 1: tile_layer<BF, RT, NW, 1, LAST>(W, b, w3, H, NT, KB, x, ld, hs, ldh, part, !LAST && over, wave, lane); break;
+        case 2: tile_layer<BF, RT, NW, 2, LAST>(W, b, w3, H, NT, KB, x, ld, hs, ldh, part, !LAST && over, wave, lane); break;
+        case 3: tile_layer<BF, RT, NW, 3, LAST>(W, b, w3, H, NT, KB, x, ld, hs, ldh, part, !LAST && over, wave, lane); break;
+        default: tile_layer<BF, RT, NW, 4, LAST>(W, b, w3, H, NT, KB, x, ld, hs, ldh, part, !LAST && over, wave, lane); break;
         }
     };
     layer(std::false_type{}, 0, b1, xs, ldx);

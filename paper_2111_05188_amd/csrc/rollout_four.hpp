@@ -269,7 +269,8 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
     // finish G tiles of layer l from t0 on: a lane has output lane % 16 of
     // env lane / 16.  Nothing is conditional, so the tiles' chains interleave:
     // a tile past the last repeats the last one's values, and outputs past
-    // the layer's (zero weights and biases) have room in their rows.
+    // the layer's have room in their rows: zeros, not what their zero weights
+    // give, which is NaN where an input is infinite.
     auto finish = [&](auto lc, auto gc, const Part &q, int t0, const auto &acc) {
         constexpr int l = decltype(lc)::value, G = decltype(gc)::value;
         const float *b = bias + (l == 0 ? 0 : l == 1 ? P.part[0].nt : P.part[0].nt + P.part[2].nt) * 16;
@@ -287,8 +288,10 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
 #pragma unroll
             for (int t = 0; t < G; ++t)
 #pragma unroll
-                for (int g = 0; g < NG; ++g)
-                    v[t][g] = BF ? tanh_for_bf16(v[t][g]) : tanh_f32(v[t][g]);
+                for (int g = 0; g < NG; ++g) {
+                    const float h = BF ? tanh_for_bf16(v[t][g]) : tanh_f32(v[t][g]);
+                    v[t][g] = BF || o[t] < q.out ? h : 0.f;   // (bf16 widths are whole tiles)
+                }
         }
 #pragma unroll
         for (int t = 0; t < G; ++t)

@@ -184,3 +184,26 @@ def test_tanh_of_the_tile_kernel(dtype):
     err = ((got - want).abs() / ulp).max().item()
     say(f"    worst error {err:.4f} ulp of {dtype}")
     assert err <= (0.5 + 1.35 * 2.0 ** -16 if bf else 1.0)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_infinite_input_at_widths_inside_a_tile(dtype):
+    """An infinite observation saturates the first hidden layer (+-1) and
+    nothing else: columns that pad the layers to whole tiles stay out."""
+    cfg = W.get_config("tiny").with_(hidden=(36, 20), dtype=dtype, E=24, L=2, n_agents=1)
+    obs, host = _obs_block(cfg, 3, 24, seed=3)
+    obs, host = obs.clone(), host.copy()
+    obs[1, 5, 7], obs[2, 9, cfg.S - 1] = float("inf"), float("-inf")
+    host[24 + 5, 7], host[48 + 9, cfg.S - 1] = np.inf, -np.inf
+    cp = W.make_critic(cfg)
+    crit = tp.CriticT([torch.from_numpy(w).cuda() for w in cp[0]],
+                      [torch.from_numpy(x).cuda() for x in cp[1]], cfg.dims[:3],
+                      tp.TP_BF16 if dtype == "bf16" else tp.TP_F32, 24)
+    crit.pack()
+    value = torch.empty(3, 24, device="cuda")
+    say(f"[critic] infinite inputs {dtype}")
+    tp.critic_value(crit, obs, value)
+    torch.cuda.synchronize()
+    want = oracle.mlp(_oracle_critic(cfg, cp, 1), 0, host[:72, :cfg.S])[:, 0]
+    assert np.isfinite(want).all()
+    rel_check("values", value.view(-1).cpu().numpy(), want, TOL_MLP[dtype])

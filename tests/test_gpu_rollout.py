@@ -313,3 +313,22 @@ def test_normals_and_log_density_against_64_bits():
     a = _rel2(pb.traj.action[0].cpu().numpy(), mu + np.exp(ls) * z)
     say(f"    logp {e:.3e} action {a:.3e}")
     assert e <= 3.0e-8 and a <= 1.1e-7
+
+
+def test_infinite_indicator_at_widths_inside_a_tile():
+    """An infinite indicator saturates the first hidden layer (+-1) and nothing
+    else: outputs that pad the four-env kernel's layers to whole tiles stay
+    out."""
+    c = W.get_config("tiny").with_(hidden=(36, 20), N=11, E=8)
+    mk = W.make_market(c)
+    mk.ind[4, 2, 1], mk.ind[6, 0, 0] = np.inf, -np.inf
+    t0 = W.make_t0(c)
+    pb, params = build_problem(c, mk, t0)
+    pb.reset()
+    say("[rollout] infinite indicators")
+    pb.rollout(SEED, 0, 10)
+    torch.cuda.synchronize()
+    teacher = pb.traj.action[:10].cpu().numpy()
+    out = oracle_replay(c, mk, params, t0, np.arange(8), SEED, 10, teacher, c.envs_per_agent)
+    assert np.isfinite(out["mu"]).all()
+    compare_rollout(c, pb, out, np.arange(8), 10)
