@@ -144,8 +144,8 @@ def main():
     pb.set_values(values)
     stream = torch.cuda.current_stream()
     torch.cuda.synchronize()
-    kname = ("rollout_rs_kernel" if tp.rollout_path(pb.mkt, pb.actor) == 1
-             else "rollout_four_kernel or rollout_kernel")
+    kname = ("rollout_kernel", "rollout_rs_kernel",
+             "rollout_four_kernel")[tp.rollout_kernel(pb.mkt, pb.actor)]
 
     for k in range(args.warmup):
         pb.step(SEED + k)

@@ -241,7 +241,9 @@ int tp_check_starts(const int64_t *t0_host, int32_t E, int64_t T1, int32_t L);
  *     the env step of tp_env_step with a;  done = (step0+j+1 == horizon).
  *   One kernel launch runs all L steps.  step0 is the episode step of the
  *   state on entry (it selects the random stream), so a rollout split into
- *   pieces with matching step0 reproduces the unsplit one bit for bit.
+ *   pieces with matching step0 reproduces the unsplit one bit for bit.  An
+ *   env's results do not depend on the other envs of the call: the first k
+ *   envs of one agent alone give the same bits as in a call over all.
  *   Requires step0 + L <= horizon.  Device-side t is not visible to the
  *   host: an env with t < 0 or t + L > T1 - 1 is not stepped: its state is
  *   left unchanged, its action / logp / reward / mu rows are NaN, done is
@@ -256,14 +258,24 @@ int tp_rollout(const tp_market *mkt, const tp_env_cfg *cfg,
                uint64_t step0, int32_t L, const tp_traj *traj, void *stream);
 
 /*
- * tp_rollout_path -- which rollout kernel tp_rollout launches for this
- * market and actor shape: 1 = the role-split kernel (bf16, 100 stocks x 4,
- * 8 or 10 indicators, S-H-H-100 with H = 256, 512, 768 or 1024, given
- * 16-byte aligned market, action and holdings-tap buffers), 0 = the four-env
- * or the generic kernel, or a negative tp_status for an invalid market or actor.  Host
- * only.
+ * tp_rollout_path -- whether tp_rollout launches the role-split kernel for
+ * this market and actor shape: 1 = yes (bf16, 100 stocks x 4, 8 or 10
+ * indicators, S-H-H-100 with H = 256, 512, 768 or 1024, given 16-byte
+ * aligned market, action and holdings-tap buffers), 0 = the four-env or the
+ * generic kernel, or a negative tp_status for an invalid market or actor.
+ * Host only.
  */
 int tp_rollout_path(const tp_market *market, const tp_actor *actor);
+
+/*
+ * tp_rollout_kernel -- which rollout kernel tp_rollout launches for this
+ * market and actor shape: 1 = the role-split kernel (as tp_rollout_path),
+ * 2 = the four-env kernel (fp32 with H1, H2 <= 1024; bf16 with H1 <= 384,
+ * H2 <= 768 whose observation rows fit its LDS), 0 = the generic kernel, or
+ * a negative tp_status.  The numbers of envs and agents play no part.  Host
+ * only.
+ */
+int tp_rollout_kernel(const tp_market *market, const tp_actor *actor);
 
 /*
  * tp_gae -- generalized advantage estimation over a rollout (PPO's

@@ -438,6 +438,14 @@ int tp_rollout_path(const tp_market *mkt, const tp_actor *actor)
     return rollout_rs_shape(lay, mkt->n * mkt->n_ind) ? 1 : 0;
 }
 
+int tp_rollout_kernel(const tp_market *mkt, const tp_actor *actor)
+{
+    const int rs = tp_rollout_path(mkt, actor);
+    PackedLayout lay;
+    if (rs != 0 || check_actor(actor, &lay) != TP_OK) return rs;
+    return rollout_four_shape(lay) ? 2 : 0;
+}
+
 int tp_rollout(const tp_market *mkt, const tp_env_cfg *cfg, const tp_env_state *st,
                const tp_actor *actor, const void *packed, size_t packed_bytes, uint64_t seed,
                uint64_t step0, int32_t L, const tp_traj *traj, void *stream)

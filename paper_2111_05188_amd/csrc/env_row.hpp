@@ -1,7 +1,7 @@
 // The stock-trading env step (paper Section 3, eqs. (2)-(4)) on one 16-lane
 // DPP row: a 64-lane wavefront steps four envs at once, env r on lanes
 // 16r .. 16r+15.  Lane s of a row holds N consecutive stocks from N s on
-// (N = 8: n <= 128; 4: n <= 64; 2: n <= 32), so
+// (N = 8: n <= 128; 2: n <= 32), so
 // stock order equals (lane, slot) order and a row's lane-order prefix sum is
 // a prefix sum in stock index order.  Every cross-lane step stays inside a
 // row (row_shr scans, quad_perm / mirror butterflies), so the four envs share
@@ -26,7 +26,7 @@
 namespace tpk {
 
 constexpr int RL = 16;    // lanes per env (one DPP row)
-constexpr int SPR = 8;    // stocks per lane (8 by default; 2 or 4 for smaller markets)
+constexpr int SPR = 8;    // stocks per lane (8 by default; 2 for markets to 32)
 
 // DPP lane moves of a 64-bit value within 16-lane rows.  Lanes without a
 // source (row_shr past the row start) receive 0.

@@ -80,8 +80,9 @@ struct RolloutArgs {
 
 hipError_t launch_rollout(RolloutArgs &a, hipStream_t s);
 hipError_t launch_rollout_rs(RolloutArgs &a, hipStream_t s);
-// the four-env kernel: hidden widths to 1,024, fp32 packed as `four`
+// the four-env kernel and its shapes (bf16 ones of the role-split kernel aside)
 hipError_t launch_rollout_four(RolloutArgs &a, hipStream_t s);
+bool rollout_four_shape(const PackedLayout &P);
 // the role-split kernel's shapes (it also needs 16-byte aligned market,
 // action and holdings-tap buffers)
 bool rollout_rs_shape(const PackedLayout &P, int nI);

@@ -478,21 +478,12 @@ hipError_t launch_rollout(RolloutArgs &a, hipStream_t s)
         const hipError_t e = launch_zero_i32(a.n_invalid, s);
         if (e != hipSuccess) return e;
     }
-    if (a.lay.four) return launch_rollout_four(a, s);
     if (a.lay.dtype == TP_BF16) {
         const hipError_t e = launch_rollout_rs(a, s);
         if (e != hipErrorNotSupported) return e;
-        // The four-env kernel, but for wide actors of many envs: it streams
-        // the weights a CU cannot keep once per 8 envs, the generic kernel
-        // once per 16.  With 1001-512-384-100 a step of 512 envs takes 17 us
-        // against 23, of 4,096 (two rounds of workgroups of 8 envs on the
-        // 256 CUs) 45 against 24; with 301-256-256-30 nearly all weights stay,
-        // and a step of 1,332 envs takes 5.1 us against 13.
-        const PackedLayout &P = a.lay;
-        const int64_t rounds = ((int64_t)a.n_agents * ((a.envs_per_agent + 7) / 8) + 255) / 256;
-        const int64_t weights = ((int64_t)P.S * P.H1 + (int64_t)P.H1 * P.H2 + (int64_t)P.H2 * P.n) * 2;
-        if (P.H1 <= 1024 && P.H2 <= 1024 && (rounds == 1 || weights <= 400 * 1024))
-            return launch_rollout_four(a, s);
+    }
+    if (rollout_four_shape(a.lay)) return launch_rollout_four(a, s);
+    if (a.lay.dtype == TP_BF16) {
         const int *k = a.lay.KS;
         // fully unrolled variants for the actor shapes in use
         if (k[0] == 32 && k[1] == 16 && k[2] == 16) return launch_cfg<__bf16, 2, 8, 32, 16, 16>(a, s);

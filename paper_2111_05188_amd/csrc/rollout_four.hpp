@@ -1,17 +1,18 @@
-// Rollout kernel for actors outside the role-split kernel's shapes (fp32
-// actors; bf16 ones of other markets and widths), hidden widths to 1,024.
-// One launch runs all L lockstep steps of 4 or 8 envs per workgroup.
+// Rollout kernel for actors outside the role-split kernel's shapes: fp32 ones
+// with hidden widths to 1,024, bf16 ones as rollout_four_shape says.  One launch
+// runs all L lockstep steps of 4, 8 or (bf16) 16 envs per workgroup.
 //
 // What bounds such a rollout is the chain of one step: a small market and a
 // small actor leave little work, and every step is layer 1 -> 2 -> 3 -> env
 // step.  Three things shorten it:
 //
-//  - MFMAs with N = 4 envs.  v_mfma_f32_4x4x1_16b_f32 (fp32) and
-//    v_mfma_f32_4x4x4_16b_bf16 multiply sixteen 4 x 4 blocks.  Four blocks
-//    take the 16 outputs of a tile, and four such sets a quarter of the inputs
-//    each: no padding of 4 envs to a tile of 16, and fragments in the layout of
-//    the 16 x 16 MFMAs.  The quarters meet by lane swaps that leave one (output,
-//    env) a lane for the bias and the tanh.
+//  - MFMAs without padding of 4 envs.  fp32: v_mfma_f32_4x4x1_16b_f32
+//    multiplies sixteen 4 x 4 blocks.  Four blocks take the 16 outputs of a
+//    tile, and four such sets a quarter of the inputs each, with fragments in
+//    the layout of the 16 x 16 MFMAs; the quarters meet by lane swaps that leave
+//    one (output, env) a lane for the bias and the tanh.  bf16: the 16 columns
+//    of v_mfma_f32_16x16x32_bf16 repeat the envs, and each lane finishes its
+//    share of its four outputs.
 //  - Weights that stay.  The LDS that rows and activations leave free is
 //    filled with weights once per launch (the action layer first, then the
 //    state columns of layer 1, layer 2, the market columns), and the matrix
@@ -21,6 +22,10 @@
 //    envs (16 lanes an env, env_row.hpp) runs the env step and an aux wave
 //    everything beside the chain: market rows, normals, observation rows.
 //    The market columns of layer 1 are multiplied while the trade runs.
+//
+// An output's sum takes its k-blocks in the same order for 4, 8 and 16 envs a
+// workgroup, whichever of them are resident, so the split does not show in the
+// results.
 //
 // Per step j, separated by workgroup barriers:
 //
@@ -33,8 +38,8 @@
 //   L3    mu = W3 h2 + b3                                     x_j to HBM, loads of row j+2
 //
 // Measured (us per lockstep step, generic kernel -> this one; whole CUs
-// streaming): 64 envs of 31-64-64-5 fp32 9.2 -> 2.4; 1,024 envs of
-// 301-256-256-30 fp32 17.5 -> 7.6; 1,332 of it in bf16 13.0 -> 5.2; 16,384 envs
+// streaming): 64 envs of 31-64-64-5 fp32 9.2 -> 2.5; 1,024 envs of
+// 301-256-256-30 fp32 17.5 -> 7.7; 1,332 of it in bf16 13.0 -> 4.9; 16,384 envs
 // of 31-64-64-5 78 -> 23.  At 31-64-64-5 the trade bounds slot A (2,100 of
 // 5,700 cycles), latencies the others.  At 301-256-256-30 fp32 loads do: 390 KB a
 // step at the CU's 64 bytes a cycle are 6,000 of 17,500 cycles, and a wave
@@ -60,7 +65,6 @@ namespace four {
 constexpr int MW = 4;       // matrix waves
 
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
-typedef short s4v __attribute__((ext_vector_type(4)));
 
 template <int I>
 using ic = std::integral_constant<int, I>;
@@ -85,7 +89,7 @@ struct Plan {
 // tiles (4 GT registers each), and k-blocks in flight for G tiles
 constexpr int keep_blocks(int GT, int NG, int TW)
 {
-    const int r = (TW == 4 ? 4 : NG == 1 ? 24 : 16) / GT;
+    const int r = (TW == 4 || NG == 4 ? 4 : NG == 1 ? 24 : 16) / GT;
     return r > 8 ? 8 : r;
 }
 constexpr int flight(int G) { return G <= 2 ? 8 : 4; }   // even: inputs take turns
@@ -105,48 +109,49 @@ __device__ __forceinline__ typename Elem<BF>::T cvt(float x)
     return (typename Elem<BF>::T)x;
 }
 
-// acc += one k-block of one tile (w) against four envs' inputs (x).  Lane l
+// Input fragments and accumulators per tile: fp32 one for every four envs, bf16
+// one for all.
+template <bool BF, int NG>
+constexpr int XS = BF ? 1 : NG;
+
+// Accumulators of G tiles.  fp32: two each for one tile at a time (narrow
+// networks and the action layer), the even and the odd elements of every
+// lane's 16 bytes, so eight partial sums an output: the sums of short layers
+// are then no further from 64 bits than those of the VALU layers of fp32
+// actors over 1,024 wide, which are split over as many lanes.
+template <bool BF, int G>
+constexpr int ACCS = !BF && G == 1 ? 2 : G;
+
+// acc += one k-block of G tiles (w) against the envs' inputs (x).  Lane l
 // holds 16 bytes of inputs kq = l / 16 of the block: in w those of output
-// l % 16, in x those of env l % 4.  Block b = l / 4 of the MFMA multiplies
-// four outputs by four envs, so lane l sums output l % 16 over its kq, for
-// the four envs in its four registers.
-template <bool BF, int E>
-__device__ __forceinline__ void mma(const u4v &w, const u4v &x, floatx4 &acc)
+// l % 16, in x those of env l % 4 (bf16: of env l % MB).
+// fp32: block b = l / 4 of the MFMA multiplies four outputs by four envs, so
+// lane l sums output l % 16 over its kq, for the four envs in its four
+// registers.  bf16: one 16 x 16 x 32 MFMA, its 16 columns the MB envs over and
+// over, so lane l has outputs 4 (l / 16) .. + 3 of env l % MB.  (It does the
+// work of four 4 x 4 x 4 ones in half their cycles where MB = 8, and leaves
+// nothing to sum over lanes: 1,332 envs of 301-256-256-30 1,442 -> 1,268 us.)
+template <bool BF, int NX, int G>
+__device__ __forceinline__ void block(const u4v *w, const u4v *x, floatx4 (&acc)[ACCS<BF, G>][NX])
 {
     if constexpr (BF) {
-        struct two {
-            s4v h[2];
-        };
-        acc = __builtin_amdgcn_mfma_f32_4x4x4bf16_1k(__builtin_bit_cast(two, x).h[E],
-                                                     __builtin_bit_cast(two, w).h[E], acc, 0, 0, 0);
-    } else {
-        acc = __builtin_amdgcn_mfma_f32_4x4x1f32(__builtin_bit_cast(floatx4, x)[E],
-                                                 __builtin_bit_cast(floatx4, w)[E], acc, 0, 0, 0);
-    }
-}
-// Accumulators of G tiles: two each for one tile at a time (narrow networks
-// and the action layer), the even and the odd elements of every lane's 16
-// bytes, so eight partial sums an output: the sums of short layers are then no
-// further from 64 bits than the VALU layers' of fp32 actors over 1,024 wide,
-// which are split over as many lanes.
-template <int G>
-constexpr int ACCS = G == 1 ? 2 : G;
-
-template <bool BF, int NG, int G>
-__device__ __forceinline__ void block(const u4v *w, const u4v *x, floatx4 (&acc)[ACCS<G>][NG])
-{
-    auto each = [&](auto e) {
-        constexpr int E = decltype(e)::value;
 #pragma unroll
         for (int t = 0; t < G; ++t)
+            acc[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w[t]),
+                                                                __builtin_bit_cast(bf16x8, x[0]),
+                                                                acc[t][0], 0, 0, 0);
+    } else {
 #pragma unroll
-            for (int g = 0; g < NG; ++g) mma<BF, E>(w[t], x[g], acc[G == 1 ? E % 2 : t][g]);
-    };
-    each(ic<0>{});
-    each(ic<1>{});
-    if constexpr (!BF) {
-        each(ic<2>{});
-        each(ic<3>{});
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int t = 0; t < G; ++t)
+#pragma unroll
+                for (int g = 0; g < NX; ++g) {
+                    floatx4 &a = acc[G == 1 ? e % 2 : t][g];
+                    a = __builtin_amdgcn_mfma_f32_4x4x1f32(__builtin_bit_cast(floatx4, x[g])[e],
+                                                           __builtin_bit_cast(floatx4, w[t])[e], a, 0,
+                                                           0, 0);
+                }
     }
 }
 
@@ -174,7 +179,7 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
                                             const uint8_t *pk, int w, int lane)
 {
     typedef typename Elem<BF>::T E;
-    constexpr int MB = 4 * NG, RU = keep_blocks(GT, NG, TW);
+    constexpr int MB = 4 * NG, RU = keep_blocks(GT, NG, TW), NX = XS<BF, NG>;
     const float *bias = (const float *)(smem + P.BIAS);
     u4v ring[16], keep[RU * GT];
     const int lo = lane * 16;
@@ -219,10 +224,10 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
         asm volatile("" : "+s"(end));
         auto inputs = [&](u4v *x, int k) {
 #pragma unroll
-            for (int g = 0; g < NG; ++g) x[g] = *(const u4v *)(xa + g * 4 * pitch + layer_block(j, k) * 64);
+            for (int g = 0; g < NX; ++g) x[g] = *(const u4v *)(xa + g * 4 * pitch + layer_block(j, k) * 64);
         };
         if (j.res > 0) {   // two blocks in turn, the next read while one is multiplied
-            u4v t[2][G], x[2][NG];
+            u4v t[2][G], x[2][NX];
             auto read = [&](int b, int k) {
                 k = min(k, j.res - 1);
 #pragma unroll
@@ -234,21 +239,21 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
             int k = 0;
             for (; k + 2 <= j.res; k += 2) {
                 read(1, k + 1);
-                block<BF, NG, G>(t[0], x[0], acc);
+                block<BF, NX, G>(t[0], x[0], acc);
                 read(0, k + 2);
-                block<BF, NG, G>(t[1], x[1], acc);
+                block<BF, NX, G>(t[1], x[1], acc);
             }
-            if (k < j.res) block<BF, NG, G>(t[0], x[0], acc);
+            if (k < j.res) block<BF, NX, G>(t[0], x[0], acc);
         }
         int k = j.res;
         if (k >= end) return;
-        u4v x[2][NG];
+        u4v x[2][NX];
         inputs(x[0], k);
         for (; k + D <= end; k += D)
 #pragma unroll
             for (int d = 0; d < D; ++d) {
                 inputs(x[(d + 1) & 1], min(k + d + 1, end - 1));
-                block<BF, NG, G>(ring + d * G, x[d & 1], acc);
+                block<BF, NX, G>(ring + d * G, x[d & 1], acc);
                 const int next = min(k + d + D, end - 1);
 #pragma unroll
                 for (int t = 0; t < G; ++t) ring[d * G + t] = gload(j, t, next);
@@ -258,31 +263,46 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
         for (int d = 0; d < D - 1; ++d)
             if (k + d < end) {
                 inputs(x[(d + 1) & 1], min(k + d + 1, end - 1));
-                block<BF, NG, G>(ring + d * G, x[d & 1], acc);
+                block<BF, NX, G>(ring + d * G, x[d & 1], acc);
             }
     };
-    // A operand: env lane % 4, inputs kq = lane / 16
-    const int xl = (lane / 16) * 16;
-    const uint8_t *x0 = smem + P.X + (lane % 4) * P.ldx + xl;
-    const uint8_t *h1 = smem + P.H1 + (lane % 4) * P.ldh1 + xl;
-    const uint8_t *h2 = smem + P.H2 + (lane % 4) * P.ldh2 + xl;
-    // finish G tiles of layer l from t0 on: a lane has output lane % 16 of
-    // env lane / 16.  Nothing is conditional, so the tiles' chains interleave:
-    // a tile past the last repeats the last one's values, and outputs past
-    // the layer's have room in their rows: zeros, not what their zero weights
-    // give, which is NaN where an input is infinite.
+    // inputs kq = lane / 16 of env lane % 4 (bf16: lane % MB)
+    const int xl = (lane / 16) * 16, xe = lane % (BF ? MB : 4);
+    const uint8_t *x0 = smem + P.X + xe * P.ldx + xl;
+    const uint8_t *h1 = smem + P.H1 + xe * P.ldh1 + xl;
+    const uint8_t *h2 = smem + P.H2 + xe * P.ldh2 + xl;
+    // finish G tiles of layer l from t0 on.  A lane takes NG (output, env) pairs
+    // of a tile: fp32 output lane % 16 of envs lane / 16 + 4 g, bf16 output
+    // 4 (lane / 16) + lane % 16 / MB NG + g of env lane % MB.  Nothing is
+    // conditional, so the tiles' chains interleave: a tile past the last repeats
+    // the last one's values, and outputs past the layer's have room in their
+    // rows: zeros, not what their zero weights give, which is NaN where an
+    // input is infinite.
     auto finish = [&](auto lc, auto gc, const Part &q, int t0, const auto &acc) {
         constexpr int l = decltype(lc)::value, G = decltype(gc)::value;
         const float *b = bias + (l == 0 ? 0 : l == 1 ? P.part[0].nt : P.part[0].nt + P.part[2].nt) * 16;
+        const int sub = lane % 16 / MB;   // bf16: which NG of a lane's outputs it takes
         int o[G];
         float v[G][NG];
 #pragma unroll
         for (int t = 0; t < G; ++t) {
-            o[t] = min(t0 + t, q.nt - 1) * 16 + lane % 16;
-            const float bo = b[o[t]];
+            o[t] = min(t0 + t, q.nt - 1) * 16 + (BF ? lane / 16 * 4 + sub * NG : lane % 16);
+            if constexpr (BF) {
+                // register sub NG + g, by compares (MB = 16: sub is 0)
+                const floatx4 &a = acc[t][0];
 #pragma unroll
-            for (int g = 0; g < NG; ++g)
-                v[t][g] = sum_kq(G == 1 ? acc[0][g] + acc[ACCS<G> - 1][g] : acc[t][g]) + bo;
+                for (int g = 0; g < NG; ++g) {
+                    float x = a[g];
+#pragma unroll
+                    for (int i = 1; i < 4 / NG; ++i) x = sub == i ? a[i * NG + g] : x;
+                    v[t][g] = x + b[o[t] + g];
+                }
+            } else {
+                const float bo = b[o[t]];
+#pragma unroll
+                for (int g = 0; g < NG; ++g)
+                    v[t][g] = sum_kq(G == 1 ? acc[0][g] + acc[ACCS<BF, G> - 1][g] : acc[t][g]) + bo;
+            }
         }
         if constexpr (l < 2) {
 #pragma unroll
@@ -297,9 +317,9 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
         for (int t = 0; t < G; ++t)
 #pragma unroll
             for (int g = 0; g < NG; ++g) {
-                const int m = g * 4 + lane / 16;
-                if constexpr (l == 2) ((float *)(smem + P.MU))[m * P.ldm + o[t]] = v[t][g];
-                else ((E *)(smem + (l == 0 ? P.H1 + m * P.ldh1 : P.H2 + m * P.ldh2)))[o[t]] = cvt<BF>(v[t][g]);
+                const int m = BF ? lane % MB : g * 4 + lane / 16, c = o[t] + (BF ? g : 0);
+                if constexpr (l == 2) ((float *)(smem + P.MU))[m * P.ldm + c] = v[t][g];
+                else ((E *)(smem + (l == 0 ? P.H1 + m * P.ldh1 : P.H2 + m * P.ldh2)))[c] = cvt<BF>(v[t][g]);
             }
     };
     auto clear = [&](auto &acc) {
@@ -328,7 +348,7 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
     for (int j = 0; j < A.L; ++j) {
         const uint8_t *x = x0 + (j & 1) * (MB * P.ldx);
         // slot A: market columns of layer 1
-        floatx4 z[TW][ACCS<GT>][NG];
+        floatx4 z[TW][ACCS<BF, GT>][NX];
 #pragma unroll
         for (int i = 0; i < TW; ++i) {
             clear(z[i]);
@@ -356,16 +376,16 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
         __syncthreads();
         // slot L2: the first group with its registers, the others streamed
         if (has2) {
-            floatx4 acc[ACCS<GT>][NG];
+            floatx4 acc[ACCS<BF, GT>][NX];
             clear(acc);
             run(g, j2, k2, h1, P.ldh1, acc);
             if (earlyA && has1) prime(g, jm, jm.kb);
             int k = k2, n = j2.kb - k2;
             asm volatile("" : "+s"(k), "+s"(n));
-            u4v x[2][NG];
+            u4v x[2][NX];
             auto inputs = [&](int b, int d) {
 #pragma unroll
-                for (int i = 0; i < NG; ++i)
+                for (int i = 0; i < NX; ++i)
                     x[b][i] = *(const u4v *)(h1 + i * 4 * P.ldh1 + (k + min(d, n - 1)) * 64);
             };
             inputs(0, 0);
@@ -373,13 +393,13 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
             for (int d = 0; d < RU; ++d)
                 if (d < n) {
                     if (d + 1 < RU) inputs((d + 1) & 1, d + 1);
-                    block<BF, NG, GT>(keep + d * GT, x[d & 1], acc);
+                    block<BF, NX, GT>(keep + d * GT, x[d & 1], acc);
                 }
             finish(ic<1>{}, g, P.part[2], t0, acc);
         }
         for (int t = t0 + MW * GT; t < P.part[2].nt; t += MW * GT) {
             const Job q = job(P.part[2], t);
-            floatx4 acc[ACCS<GT>][NG];
+            floatx4 acc[ACCS<BF, GT>][NX];
             clear(acc);
             prime(g, q, q.kb);
             run(g, q, q.kb, h1, P.ldh1, acc);
@@ -391,7 +411,7 @@ __device__ __forceinline__ void matrix_role(const RolloutArgs &A, const Plan &P,
         // slot L3 (at most two tiles a wave)
         for (int t = w; t < P.part[3].nt; t += MW) {
             const Job q = job(P.part[3], t);
-            floatx4 acc[ACCS<1>][NG];
+            floatx4 acc[ACCS<BF, 1>][NX];
             clear(acc);
             if (t != w) prime(ic<1>{}, q, q.kb);
             run(ic<1>{}, q, q.kb, h2, P.ldh2, acc);
@@ -725,11 +745,10 @@ __global__ __launch_bounds__((MW + 2 * NG) * WAVE) void rollout_four_kernel(Roll
 // envs' 64 bytes of a k-block fall on different banks
 inline int pitch(int bytes) { return (bytes - 64 + 255) / 256 * 256 + 64; }
 
-inline bool make_plan(const RolloutArgs &a, int MB, int GT, int TW, int budget, Plan *P)
+inline bool make_plan(const PackedLayout &L, int MB, int GT, int TW, int budget, Plan *P)
 {
-    const PackedLayout &L = a.lay;
     const int es = L.dtype == TP_BF16 ? 2 : 4, per = 64 / es;
-    const int n = a.env.n, S = 1 + 2 * n + a.env.nI;
+    const int n = L.n, S = L.S;
     auto blocks = [&](int k) { return (k + per - 1) / per; };
     // layer 1's state blocks: block 0 (the balance) and b0 .. b1 (the
     // holdings, columns n + 1 .. 2n)
@@ -750,7 +769,7 @@ inline bool make_plan(const RolloutArgs &a, int MB, int GT, int TW, int budget, 
     }
     const int N = n <= 32 ? 2 : 8;
     P->ldm = RL * N;
-    P->ldx = pitch(blocks(a.env.K_pad) * 64);
+    P->ldx = pitch(blocks(L.K_pad) * 64);
     P->ldh1 = pitch(u2 * 64);
     P->ldh2 = pitch(u3 * 64);
     int o = 0;
@@ -798,27 +817,40 @@ hipError_t launch_cfg(RolloutArgs &a, const Plan &P, hipStream_t s)
     return hipGetLastError();
 }
 
-// NG env groups of four and the hidden widths' tile groups
+// The hidden widths' tile groups
+struct Tiles {
+    int GT, TW;
+};
+inline Tiles tiles(const PackedLayout &L)
+{
+    const int H = L.H1 > L.H2 ? L.H1 : L.H2, nt1 = (L.H1 + 15) / 16;
+    const int GT = H <= 64 ? 1 : H <= 128 ? 2 : nt1 > 4 * MW && nt1 <= 6 * MW ? 3 : 4;
+    return {GT, nt1 <= GT * MW ? 1 : GT == 3 ? 2 : 4};
+}
+
+// NG env groups of four
 template <bool BF, int NG, int N>
 hipError_t launch_width(RolloutArgs &a, hipStream_t s)
 {
-    const int H = a.lay.H1 > a.lay.H2 ? a.lay.H1 : a.lay.H2, nt1 = (a.lay.H1 + 15) / 16;
-    const int GT = H <= 64 ? 1 : H <= 128 ? 2 : nt1 > 4 * MW && nt1 <= 6 * MW ? 3 : 4;
-    const int TW = nt1 <= GT * MW ? 1 : GT == 3 ? 2 : 4;
+    const Tiles t = tiles(a.lay);
     Plan P;
-    if (!make_plan(a, 4 * NG, GT, TW, (int)LDS_LIMIT, &P)) return hipErrorNotSupported;
-    if (GT == 1) return launch_cfg<BF, NG, 1, 1, N>(a, P, s);
-    if (GT == 2) return launch_cfg<BF, NG, 2, 1, N>(a, P, s);
-    if (GT == 3) return launch_cfg<BF, NG, 3, 2, N>(a, P, s);
-    if (TW == 1) return launch_cfg<BF, NG, 4, 1, N>(a, P, s);
-    return launch_cfg<BF, NG, 4, 4, N>(a, P, s);
+    if (!make_plan(a.lay, 4 * NG, t.GT, t.TW, (int)LDS_LIMIT, &P)) return hipErrorNotSupported;
+    if (t.GT == 2) return launch_cfg<BF, NG, 2, 1, N>(a, P, s);
+    if (t.GT == 3) return launch_cfg<BF, NG, 3, 2, N>(a, P, s);
+    if constexpr (!BF) {   // (bf16 widths are multiples of 128, first layers at most 384 wide)
+        if (t.GT == 1) return launch_cfg<BF, NG, 1, 1, N>(a, P, s);
+        if (t.TW == 4) return launch_cfg<BF, NG, 4, 4, N>(a, P, s);
+    }
+    return launch_cfg<BF, NG, 4, 1, N>(a, P, s);
 }
 
 template <bool BF, int N>
 hipError_t launch_type(RolloutArgs &a, hipStream_t s)
 {
-    const int blocks4 = a.n_agents * ((a.envs_per_agent + 3) / 4);
-    if (blocks4 > 256) {
+    auto blocks = [&](int MB) { return (int64_t)a.n_agents * ((a.envs_per_agent + MB - 1) / MB); };
+    if constexpr (BF)   // (every bf16 shape taken fits 16 envs)
+        if (blocks(8) > 256) return launch_width<BF, 4, N>(a, s);
+    if (blocks(4) > 256) {
         const hipError_t e = launch_width<BF, 2, N>(a, s);
         if (e != hipErrorNotSupported) return e;
     }

@@ -85,6 +85,7 @@ EXPORTS = ("tp_env_reset", "tp_env_step", "tp_actor_packed_bytes",
            "tp_keep_best", "tp_select",
            "tp_ppo_param_count", "tp_ppo_workspace_bytes", "tp_ppo_update",
            "tp_ppo_update_agents", "tp_minibatch_rows", "tp_rollout_path",
+           "tp_rollout_kernel",
            "tp_actor_release", "tp_critic_release", "tp_check_starts",
            "tp_backtest_metrics_noalloc",
            "tp_last_error", "tp_version")
@@ -127,6 +128,7 @@ def load(path: str = LIB_PATH):
     L.tp_ppo_workspace_bytes.restype = C.c_size_t
     L.tp_ppo_workspace_bytes.argtypes = [vp]
     L.tp_rollout_path.argtypes = [vp, vp]
+    L.tp_rollout_kernel.argtypes = [vp, vp]
     L.tp_minibatch_rows.argtypes = [C.c_uint64, C.c_uint64, i32, i32, i32, i32, i32, i32, vp,
                                     vp]
     L.tp_ppo_update.argtypes = [vp, vp, vp, vp, i64, i32, vp, i64, vp, vp, vp, vp, i64, vp,
@@ -602,6 +604,15 @@ def minibatch_rows(seed: int, counter: int, n_updates: int, B: int, L: int, E: i
 def rollout_path(mkt: MarketT, actor: ActorT) -> int:
     """1 if tp_rollout runs the role-split kernel for this shape, else 0."""
     r = load().tp_rollout_path(C.byref(mkt.s), C.byref(actor.s))
+    if r < 0:
+        _check(r)
+    return r
+
+
+def rollout_kernel(mkt: MarketT, actor: ActorT) -> int:
+    """The kernel tp_rollout runs for this shape: 1 the role-split, 2 the
+    four-env, 0 the generic one."""
+    r = load().tp_rollout_kernel(C.byref(mkt.s), C.byref(actor.s))
     if r < 0:
         _check(r)
     return r

@@ -109,6 +109,33 @@ def test_rollout_path_host_only():
     assert L.tp_rollout_path(C.byref(m), C.byref(_nasdaq_actor(dims=(1001, 500, 512, 100)))) < 0
 
 
+def test_rollout_kernel_host_only():
+    """Which of the three rollout kernels a shape gets: 1 role-split, 2
+    four-env, 0 generic.  The shape decides, whatever the number of envs and
+    agents (an env's results must not depend on the others in the call)."""
+    L = tp.load()
+    x = 0x100000
+
+    def kernel(n, I, h1, h2, dtype, agents=1, epa=4096):
+        a = _nasdaq_actor(dtype, (1 + 2 * n + n * I, h1, h2, n), agents)
+        a.envs_per_agent = epa
+        return L.tp_rollout_kernel(C.byref(tp.Market(x, x, 100, n, I)), C.byref(a))
+
+    F, B = tp.TP_F32, tp.TP_BF16
+    for shape, want in (((100, 8, 512, 512, B), 1), ((100, 4, 256, 256, B), 1),
+                        ((100, 8, 512, 512, F), 2), ((5, 4, 4, 4, F), 2), ((30, 8, 1024, 1024, F), 2),
+                        ((30, 8, 1028, 64, F), 0), ((30, 8, 64, 1028, F), 0),
+                        ((30, 8, 256, 256, B), 2), ((1, 0, 384, 768, B), 2),
+                        ((5, 4, 512, 128, B), 0), ((5, 4, 384, 896, B), 0),
+                        ((100, 8, 384, 256, B), 2), ((100, 8, 512, 384, B), 0),
+                        ((128, 8, 384, 512, B), 2),
+                        # rows of 16 envs do not fit the LDS beside a second layer of 768
+                        ((128, 8, 384, 768, B), 0)):
+        for agents, epa in ((1, 1), (1, 512), (1, 4096), (16, 333), (1, 1 << 20)):
+            assert kernel(*shape, agents, epa) == want, (shape, agents, epa)
+    assert kernel(30, 8, 100, 128, B) < 0
+
+
 def test_argument_errors_without_gpu():
     L = tp.load()
     assert L.tp_gae(None, None, None, 1, 1, 0.99, 0.95, None, None, None) == tp.TP_EINVAL

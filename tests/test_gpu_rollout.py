@@ -126,24 +126,77 @@ def test_largest_market(dtype):
     assert tp.rollout_path(pb.mkt, pb.actor) == 0
 
 
-@pytest.mark.parametrize("n,I,hidden,E,L,agents,dtype", [
-    (1, 0, (4, 4), 1, 1, 1, "f32"),          # one stock, no indicators, one k-block
-    (8, 8, (16, 16), 5, 2, 1, "f32"),        # holdings end on a k-block's edge
-    (5, 4, (96, 36), 1030, 3, 1, "f32"),     # eight envs a workgroup, a ragged last one
-    (33, 8, (320, 192), 9, 4, 3, "f32"),     # eight stocks a lane, two tile groups of layer 1
-    (20, 8, (1024, 500), 6, 3, 1, "f32"),    # four groups; layers that stream
-    (5, 4, (1028, 64), 6, 3, 1, "f32"),      # wider than the kernel: the generic one
-    (31, 3, (256, 128), 1100, 3, 2, "bf16"),
-    (64, 4, (128, 384), 21, 2, 3, "bf16"),
-    (128, 8, (640, 128), 7, 3, 1, "bf16"),
-    (100, 5, (256, 384), 2064, 2, 1, "bf16"),    # many envs of a wide actor: the generic kernel
+GENERIC, FOUR = 0, 2   # tp_rollout_kernel
+
+
+@pytest.mark.parametrize("n,I,hidden,E,L,agents,dtype,kernel", [
+    (1, 0, (4, 4), 1, 1, 1, "f32", FOUR),          # one stock, no indicators, one k-block
+    (8, 8, (16, 16), 5, 2, 1, "f32", FOUR),        # holdings end on a k-block's edge
+    (5, 4, (96, 36), 1030, 3, 1, "f32", FOUR),     # eight envs a workgroup, a ragged last one
+    (33, 8, (320, 192), 9, 4, 3, "f32", FOUR),     # eight stocks a lane, two tile groups of layer 1
+    (20, 8, (1024, 500), 6, 3, 1, "f32", FOUR),    # four groups; layers that stream
+    (5, 4, (1028, 64), 6, 3, 1, "f32", GENERIC),   # wider than the kernel
+    (31, 3, (256, 128), 1100, 3, 2, "bf16", FOUR),
+    (64, 4, (128, 384), 21, 2, 3, "bf16", FOUR),
+    (128, 8, (640, 128), 7, 3, 1, "bf16", GENERIC),
+    (100, 5, (256, 384), 2064, 2, 1, "bf16", FOUR),    # sixteen envs a workgroup
 ])
-def test_four_env_kernel_edges(n, I, hidden, E, L, agents, dtype):
+def test_four_env_kernel_edges(n, I, hidden, E, L, agents, dtype, kernel):
     cfg = W.get_config("tiny").with_(name=f"four-{n}", n=n, n_ind=I, hidden=hidden, dtype=dtype)
     ids = None if E < 100 else np.r_[0:5, E // agents - 3:E // agents + 3, E - 9:E]
     ids = ids if ids is None else np.unique(ids[ids < E])
     pb = _run_case(cfg, E, L, rows=8, n_agents=agents, cmp_ids=ids)
     assert tp.rollout_path(pb.mkt, pb.actor) == 0
+    assert tp.rollout_kernel(pb.mkt, pb.actor) == kernel
+
+
+# Every instantiation of the four-env kernel: tile groups (GT, TW) by the
+# hidden widths, two or eight stocks a lane, and envs a workgroup by the env
+# count (4 up to 256 workgroups, then 8, for bf16 then 16).  The env counts
+# end inside a workgroup's second group of four; several agents are ragged each.
+@pytest.mark.parametrize("n,I", [(5, 4), (33, 3)])
+@pytest.mark.parametrize("hidden,dtype", [
+    ((64, 32), "f32"), ((128, 128), "f32"), ((320, 192), "f32"), ((256, 256), "f32"),
+    ((1024, 64), "f32"),
+    ((128, 128), "bf16"), ((384, 384), "bf16"), ((256, 256), "bf16"), ((128, 768), "bf16"),
+])
+@pytest.mark.parametrize("E,agents", [(11, 1), (1037, 1), (3 * 345, 3), (2063, 1), (3 * 691, 3)])
+def test_four_env_kernel_variants(n, I, hidden, dtype, E, agents):
+    cfg = W.get_config("tiny").with_(name=f"four-{n}", n=n, n_ind=I, hidden=hidden, dtype=dtype)
+    epa = E // agents
+    ids = np.unique(np.r_[0:min(9, epa), epa - 3:epa, E - 5:E])
+    pb = _run_case(cfg, E, 3, rows=8, n_agents=agents, cmp_ids=ids)
+    assert tp.rollout_kernel(pb.mkt, pb.actor) == FOUR
+
+
+@pytest.mark.parametrize("n,I,hidden,dtype,kernel", [
+    (5, 4, (64, 64), "f32", FOUR), (33, 3, (320, 192), "f32", FOUR), (30, 8, (256, 256), "f32", FOUR),
+    (5, 4, (1028, 64), "f32", GENERIC),
+    (30, 8, (256, 256), "bf16", FOUR), (33, 3, (384, 384), "bf16", FOUR),
+    (100, 8, (384, 256), "bf16", FOUR), (100, 8, (512, 384), "bf16", GENERIC),
+])
+def test_results_do_not_depend_on_the_number_of_envs(n, I, hidden, dtype, kernel):
+    """The first envs of a call alone give the same bits as among 1,040 and
+    2,064 envs, where workgroups take more envs each (and a bf16 kernel chosen
+    by the number of envs would be another one)."""
+    cfg = W.get_config("tiny").with_(name=f"envs-{n}", n=n, n_ind=I, hidden=hidden, dtype=dtype,
+                                     N=30, L=6)
+    mk = W.make_market(cfg)
+    runs = []
+    for E in (11, 1040, 2064):
+        t0 = np.arange(E, dtype=np.int64) % 20
+        pb, _ = build_problem(cfg.with_(E=E), mk, t0)
+        pb.reset()
+        say(f"[rollout] {E} envs, {n} stocks {hidden} {dtype}")
+        pb.rollout(SEED, 0, 6)
+        torch.cuda.synchronize()
+        assert tp.rollout_kernel(pb.mkt, pb.actor) == kernel
+        runs.append(pb)
+    for pb in runs[1:]:
+        for name in ("action", "logp", "reward", "mu_tap", "cash_tap", "shares_tap", "obs"):
+            a, b = getattr(runs[0].traj, name), getattr(pb.traj, name)
+            assert torch.equal(a[:, :11], b[:, :11]), name
+        assert torch.equal(runs[0].traj.obs_last, pb.traj.obs_last[:11])
 
 
 def test_bf16_100_stock_actor_outside_the_role_split_shapes():
@@ -246,6 +299,48 @@ def test_env_without_room_role_split_kernel():
     teacher = pb.traj.action[:30].index_select(1, torch.as_tensor(ids, device="cuda")).cpu().numpy()
     out = oracle_replay(cfg, mk, params, t0[ids], ids, SEED, 30, teacher, cfg.envs_per_agent)
     compare_rollout(cfg, pb, out, ids, 30)
+
+
+@pytest.mark.parametrize("n,I,hidden,dtype,E,kernel", [
+    (5, 4, (1028, 64), "f32", 21, GENERIC),
+    (5, 4, (512, 128), "bf16", 37, GENERIC),
+    (5, 4, (64, 64), "f32", 1037, FOUR),
+    (33, 3, (256, 128), "bf16", 2063, FOUR),
+])
+def test_env_without_room_other_kernels(n, I, hidden, dtype, E, kernel):
+    """Envs that cannot be stepped on the generic kernel and on the four-env
+    kernel with 8 and 16 envs a workgroup: NaN rows, done 0, taps that repeat
+    the state, the state unchanged, both counted; the others as the oracle."""
+    cfg = W.get_config("tiny").with_(name=f"room-{n}", n=n, n_ind=I, hidden=hidden, dtype=dtype,
+                                     N=40, E=E, L=20)
+    mk = W.make_market(cfg)
+    t0 = W.make_t0(cfg)
+    pb, params = build_problem(cfg, mk, t0)
+    assert tp.rollout_kernel(pb.mkt, pb.actor) == kernel
+    pb.state = tp.StateT.empty(E, n, count_invalid=True)
+    pb.reset()
+    bad = [6, E - 2]
+    pb.state.t[bad[0]], pb.state.t[bad[1]] = cfg.T1 - 5, -7
+    pb.state.cash[bad[0]] = 1234.5
+    pb.state.shares[bad[0], n - 1] = 3
+    say(f"[rollout] envs without room, {n} stocks {hidden} {dtype}, {E} envs")
+    pb.rollout(SEED, 0, 20)
+    torch.cuda.synchronize()
+    tr = pb.traj
+    assert pb.state.n_invalid.item() == 2
+    for x in (tr.action, tr.logp, tr.reward, tr.mu_tap, tr.asset_tap):
+        assert torch.isnan(x[:20, bad]).all()
+    assert (tr.done[:20, bad] == 0).all()
+    assert (tr.cash_tap[:20, bad[0]] == 1234.5).all()
+    want = torch.zeros(n, dtype=torch.int32, device="cuda")
+    want[n - 1] = 3
+    assert (tr.shares_tap[:20, bad[0]] == want).all() and (tr.shares_tap[:20, bad[1]] == 0).all()
+    assert pb.state.t[bad].tolist() == [cfg.T1 - 5, -7]
+    assert pb.state.cash[bad[0]].item() == 1234.5 and (pb.state.shares[bad[0]] == want).all()
+    ids = np.array([0, 4, 5, 7, E - 3, E - 1])
+    teacher = tr.action[:20].index_select(1, torch.as_tensor(ids, device="cuda")).cpu().numpy()
+    out = oracle_replay(cfg, mk, params, t0[ids], ids, SEED, 20, teacher, cfg.envs_per_agent)
+    compare_rollout(cfg, pb, out, ids, 20)
 
 
 def test_rollout_errors():
