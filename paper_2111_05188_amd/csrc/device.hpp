@@ -148,6 +148,17 @@ __device__ __forceinline__ float lane_value(float v, int lane)
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
 }
 
+// Orders this wave's LDS writes before the reads that other lanes of it make
+// after (and its reads before the next writes).  One wave's LDS operations
+// complete in order, so it costs no instruction: it keeps the compiler from
+// moving them over one another.
+__device__ __forceinline__ void wave_lds_fence()
+{
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // Sum over the 64 lanes (same value returned to every lane).
 __device__ __forceinline__ double wave_sum(double v)
 {

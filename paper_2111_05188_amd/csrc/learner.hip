@@ -223,8 +223,8 @@ __global__ __launch_bounds__(NW *WAVE) void gemm_split_kernel(GemmBatch gb)
             pb[i] = (const E *)P.B + (size_t)min(n0 + i * 16 + lr, P.N - 1) * P.ldb + wave * KB +
                     lp * (16 / (int)sizeof(E));
         }
-        // and goes through 1 KiB of this wave's LDS to the MFMA's lanes (LDS
-        // operations of one wave complete in order: no barrier).  Piece p of
+        // and goes through 1 KiB of this wave's LDS to the MFMA's lanes (no
+        // barrier: wave_lds_fence).  Piece p of
         // row r sits at p ^ (r / 4), so neither side has bank conflicts.
         char *stage = (char *)&red[0][0][0] + wave * (2 * F * 1024);
         const int st = lr * 64 + ((lp ^ (lr >> 2)) * 16);
@@ -247,11 +247,13 @@ __global__ __launch_bounds__(NW *WAVE) void gemm_split_kernel(GemmBatch gb)
                 *(frag *)(stage + i * 1024 + st) = la[i];
                 *(frag *)(stage + (F + i) * 1024 + st) = lb[i];
             }
+            wave_lds_fence();
 #pragma unroll
             for (int i = 0; i < F; ++i) {
                 xa[i] = *(const frag *)(stage + i * 1024 + ld);
                 xb[i] = *(const frag *)(stage + (F + i) * 1024 + ld);
             }
+            wave_lds_fence();   // read before the next block is written
             if constexpr (BF) {
 #pragma unroll
                 for (int i = 0; i < F; ++i)
