@@ -222,9 +222,12 @@ int check_critic(const tp_critic *c, CriticLayout *lay)
     if (H1 % 4 || H2 % 4)
         return fail(TP_EUNSUPPORTED, "critic needs H1, H2 multiples of 4 (got %d, %d)", H1, H2);
     critic_layout(c, lay);
-    if (!lay->mfma && (size_t)16 * (lay->K_pad + H1 + 256) * 4 > LDS_LIMIT)
-        return fail(TP_EUNSUPPORTED, "critic {%d,%d,%d} exceeds the generic kernel's working set",
-                    S, H1, H2);
+    // 16 fp32 rows and their first hidden layer within 144 KiB: the accepted
+    // set for both types.  The tile kernel needs less for 16 rows (bf16 half of
+    // it), so every accepted critic launches.
+    static_assert(16 * (4 * 2304 + 2 * 16 + 60 + 16) <= LDS_LIMIT, "rows, pitches' padding, partials");
+    if (!lay->mfma && lay->K_pad + H1 > 2304)
+        return fail(TP_EUNSUPPORTED, "critic {%d,%d,%d} needs K_pad + H1 <= 2304", S, H1, H2);
     return TP_OK;
 }
 

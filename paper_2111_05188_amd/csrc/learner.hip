@@ -165,8 +165,8 @@ __device__ __forceinline__ void static_for(Fn &&fn)
     }
 }
 
-// Products split over the waves of a workgroup (fp32, and bf16 where K is
-// none of the staged kernels'): a tile of 16 F x 16 F, the NW waves taking
+// Products split over the waves of a workgroup (fp32, and bf16 where neither K
+// nor the tile count, LDS_MIN_TILES, sends them to the staged kernels): a tile of 16 F x 16 F, the NW waves taking
 // k-blocks w, w + NW, ... of it (64 bytes of every row: 16 fp32 or 32 bf16),
 // each with F x F accumulators of 16 x 16.  Loads are 16 bytes a lane, four
 // consecutive lanes on 64 contiguous bytes of a row, D blocks ahead in
@@ -371,8 +371,8 @@ __global__ __launch_bounds__(NW *WAVE) void gemm_split_kernel(GemmBatch gb)
     }
 }
 
-// bf16 through LDS, for products whose K is a multiple of 128 (all of the
-// bf16 learner's): chunks of 64 rows x 128 k of A and of B are staged in
+// bf16 through LDS, for products with K = 128, 512 or 1,024 (unrolled) and, from
+// LDS_MIN_TILES tiles on, any multiple of 32: chunks of 64 rows x 128 k of A and of B are staged in
 // LDS (rows padded by 32 bytes, measured faster than 16 or 48), loaded
 // with whole-line accesses (each wave instruction
 // reads 4 rows x 256 contiguous bytes), GEMM_LD chunks ahead in registers

@@ -396,6 +396,7 @@ def test_partial_column_blocks_in_staged_products():
     (33, (288, 64), 96, "f32"),      # action columns past one tile
     (3, (32, 4128), 32, "f32"),      # a critic head wider than the loss kernel stages at a time
     (3, (64, 2080), 32, "f32"),      # a head of many rounds, half a column tile last
+    (3, (32, 4128), 32, "bf16"),     # the same in bf16
     (5, (32, 32), 32, "bf16"),       # K = 32: one k-block
     (7, (96, 224), 160, "bf16"),
     (33, (288, 64), 96, "bf16"),
@@ -408,12 +409,26 @@ def test_products_split_over_the_waves(n, hidden, B, dtype):
     _check_grad(r["dims"], r["grad"], r["g_o"], GRAD_TOL[dtype], f"{n} {hidden} {B} {dtype}")
 
 
+def _lds_any_k_groups(dims, B):
+    """The grouped products of one update, in order, that the 64 x 64 LDS
+    kernel takes with its run-time k-loop: 200 or more tiles in one learner and
+    a K that is none of 128, 512 and 1,024."""
+    S, H1, H2, n, C1, C2 = dims
+    Kp, n_pad = -(-S // 32) * 32, -(-n // 32) * 32
+    groups = [[(B, H1 + C1, Kp)], [(B, H2, H1), (B, C2, C1)], [(B, n, H2)],
+              [(n, H2, B), (B, H2, n_pad), (C2, C1, B), (B, C1, C2)],
+              [(H2, H1, B), (B, H1, H2)], [(H1 + C1, S, B)]]
+    tiles = [sum(-(-M // 64) * -(-N // 64) for M, N, _ in g) for g in groups]
+    return [i for i, g in enumerate(groups)
+            if tiles[i] >= 200 and any(K not in (128, 512, 1024) for _, _, K in g)]
+
+
 @pytest.mark.parametrize("n,hidden,B", [
     (9, (1056, 1056), 416),   # K = 1056 (a quarter chunk last), 416, 64 inputs; ragged tiles
     (33, (672, 608), 1312),   # K = 1312, 672, 608: an odd chunk last, actions past 32
     (3, (32, 32), 6400),      # 200 row tiles of one 32-input chunk (no pair, half a tile)
-    (3, (32, 4128), 32),      # a critic head wider than the loss kernel stages at a time
-    (100, (512, 512), 2048),  # K = 2048: whole chunks of another count, 576-column inputs
+    (3, (32, 4256), 32),      # 202 tiles of one 32-input chunk and one of 4,256; a wide head
+    (100, (512, 512), 2048),  # K = 2048: whole chunks of another count, 608-column inputs
 ])
 def test_products_through_lds_any_k(n, hidden, B):
     """bf16 products with many tiles and another K than the unrolled ones,
@@ -427,6 +442,7 @@ def test_products_through_lds_any_k(n, hidden, B):
     single element of 300,000 lies near 0.023 of its segment's RMS in any
     order of the sums, so GRAD_TOL is for smaller networks.)"""
     cfg = W.get_config("tiny").with_(name=f"lds-{n}", n=n, hidden=hidden, dtype="bf16")
+    assert _lds_any_k_groups(_dims(cfg), B)
     r = _run(cfg, B, B, 1)
     g, o = (ppo.unflatten(np.asarray(x, dtype=np.float64), r["dims"]) for x in (r["grad"], r["g_o"]))
     for name, _ in ppo.layout(*r["dims"]):
