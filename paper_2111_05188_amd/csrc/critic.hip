@@ -23,7 +23,8 @@
 // with the staging loads ahead of the weights: each chunk then waited for
 // HBM); 72 envs of four agents x 391 steps in 53 us (299 us with a block per
 // step and agent: 18 of its 128 rows).  101 x 728 rows of 1001-1024-1024 in
-// 0.315 ms (0.321).
+// 0.315 ms (0.321).  (The 512-wide kernel is at its 256 registers and spills
+// 8 of them, which the times include.)
 //
 // Every other shape (fp32, or bf16 of other widths) runs the tile kernel
 // below.
@@ -290,7 +291,7 @@ __global__ __launch_bounds__(NW *WAVE, CRITIC_MIN_WAVES) void critic_mfma_kernel
 // observation rows' place (a third workgroup then fits a CU).
 //
 // fp32 is bound by its MFMAs: a year of the 30-stock daily workload (253 x
-// 1,024 rows, 301-256-256) takes 0.70 ms, 105 TFLOP/s of the 153 a large
+// 1,024 rows, 301-256-256) takes 0.71 ms, 104 TFLOP/s of the 153 a large
 // fp32 product reaches; 0.68 ms without the tanh.  The kernel before it (one
 // VALU thread an output, 16 rows a workgroup) took 2.26 ms, and 2.21 ms with
 // bf16 rows, where this one takes 0.18 (1.00 against 0.11 at 298-128-352,

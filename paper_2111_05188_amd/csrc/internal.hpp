@@ -37,11 +37,11 @@ struct EnvConst {
 //  * 16].
 struct PackedLayout {
     int dtype;
-    bool four;
+    bool four;            // fp32 packed for the four-env kernel
     int S, H1, H2, n;
     int K_pad;
-    int NT[3];            // output tiles of 16 (bf16)
-    int KS[3];            // k-steps of 32 (bf16) / k-blocks of 4 (f32)
+    int NT[3];            // output tiles of 16 (f32 transposes: outputs)
+    int KS[3];            // k-steps of 32 (bf16) or 16 (four), k-blocks of 4 (f32)
     size_t off_W[3], off_b[3], off_ls;
     size_t agent_stride;
     size_t total;

@@ -88,7 +88,7 @@ def test_rollout_path_host_only():
     """Which rollout kernel a market and actor shape get, decided on the
     host: the role-split kernel for 100 stocks with 4, 8 or 10 indicators
     each and two equal bf16 hidden layers of 256 to 1024 (multiples of 256),
-    the generic one otherwise."""
+    another one (0) otherwise."""
     L = tp.load()
     x = 0x100000
     m = tp.Market(x, x, 100, 100, 8)

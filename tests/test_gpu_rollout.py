@@ -200,8 +200,8 @@ def test_results_do_not_depend_on_the_number_of_envs(n, I, hidden, dtype, kernel
 
 
 def test_bf16_100_stock_actor_outside_the_role_split_shapes():
-    # unequal hidden widths (512-256) on the 100 x 8 market: the four-env
-    # kernel takes it, with the same results contract
+    # unequal hidden widths (512-256) on the 100 x 8 market: the generic kernel
+    # takes it, with the same results contract
     cfg = W.get_config("nasdaq100").with_(hidden=(512, 256))
     pb = _run_case(cfg, 21, 30, rows=20 * 390 + 1)
     assert tp.rollout_path(pb.mkt, pb.actor) == 0

@@ -57,7 +57,7 @@ def _spread(blocks, per_block, block_envs, seed):
 def test_dow30_full():
     cfg = W.get_config("dow30")
     mk = W.make_market(cfg)
-    # 4 envs per workgroup on the generic kernel: 32 envs spread over all 256
+    # 4 envs per workgroup on the four-env kernel: 32 envs spread over all 256
     _full(cfg, mk, [0, 1, 1023] + _spread(256, 9, 4, 1))
 
 
