@@ -245,6 +245,62 @@ def test_deterministic_and_resumable():
         assert torch.equal(getattr(pb.state, s), getattr(a.state, s)), s
 
 
+@pytest.mark.parametrize("n,I,hidden,dtype,E", [
+    (5, 4, (64, 64), "f32", 11), (33, 3, (256, 128), "f32", 1037),
+    (30, 8, (256, 256), "bf16", 1100), (33, 3, (384, 384), "bf16", 2063),
+])
+def test_four_env_kernel_resumes(n, I, hidden, dtype, E):
+    """rollout(9) equals rollout(4) and rollout(5, step0=4) from the saved state,
+    with 4, 8 and 16 envs a workgroup (an odd split: both row buffers start)."""
+    cfg = W.get_config("tiny").with_(name=f"resume-{n}", n=n, n_ind=I, hidden=hidden, dtype=dtype,
+                                     N=30, E=E, L=9)
+    mk = W.make_market(cfg)
+    t0 = np.arange(E, dtype=np.int64) % 20
+    whole, _ = build_problem(cfg, mk, t0)
+    split, _ = build_problem(cfg, mk, t0)
+    assert tp.rollout_kernel(whole.mkt, whole.actor) == FOUR
+    whole.reset()
+    split.reset()
+    dt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    parts = [tp.TrajT.alloc(k, E, n, cfg.K_pad, dt, taps=True, obs_last=True) for k in (4, 5)]
+    say(f"[rollout] resume, {n} stocks {hidden} {dtype}, {E} envs")
+    whole.rollout(SEED, 0, 9)
+    split.rollout(SEED, 0, 4, traj=parts[0])
+    split.rollout(SEED, 4, 5, traj=parts[1])
+    torch.cuda.synchronize()
+    for name in ("action", "logp", "reward", "done", "cash_tap", "shares_tap", "mu_tap", "obs"):
+        both = torch.cat([getattr(q, name) for q in parts])
+        assert torch.equal(getattr(whole.traj, name)[:9], both), name
+    assert torch.equal(parts[0].obs_last, whole.traj.obs[4])
+    assert torch.equal(parts[1].obs_last, whole.traj.obs_last)
+    for name in ("cash", "shares", "t"):
+        assert torch.equal(getattr(whole.state, name), getattr(split.state, name)), name
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_agents_of_one_call_equal_single_calls(dtype):
+    """Three agents of 700 envs in one call: every agent's means on the first
+    bar are those of a call over it alone (8 or 16 envs a workgroup against 4
+    or 8; the action noise is drawn per agent, so only the means compare)."""
+    cfg = W.get_config("tiny").with_(name="agents", n=30, n_ind=8, hidden=(256, 128), dtype=dtype,
+                                     N=30, E=2100, n_agents=3, L=1)
+    mk = W.make_market(cfg)
+    t0 = np.arange(2100, dtype=np.int64) % 20
+    pb, (Wl, b, ls) = build_problem(cfg, mk, t0)
+    assert tp.rollout_kernel(pb.mkt, pb.actor) == FOUR
+    pb.reset()
+    pb.rollout(SEED, 0, 1)
+    for a in range(3):
+        sl = slice(a, a + 1)
+        one, _ = build_problem(cfg.with_(E=700, n_agents=1), mk, t0[700 * a:700 * (a + 1)],
+                               params=([w[sl] for w in Wl], [x[sl] for x in b], ls[sl]))
+        one.reset()
+        say(f"[rollout] agent {a} alone, {dtype}")
+        one.rollout(SEED, 0, 1)
+        torch.cuda.synchronize()
+        assert torch.equal(pb.traj.mu_tap[0, 700 * a:700 * (a + 1)], one.traj.mu_tap[0]), a
+
+
 def test_env_without_room_is_not_stepped():
     cfg = W.get_config("tiny")
     mk = W.make_market(cfg)
