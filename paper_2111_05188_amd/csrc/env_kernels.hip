@@ -87,7 +87,7 @@ __global__ __launch_bounds__(ENV_WPB *WAVE) void env_step_kernel(
     // nothing); loads use valid addresses only
     const bool in = e < E;
     const int64_t tt = in ? t[e] : -1;
-    const bool live = in && tt >= 0 && tt + 1 < C.T1;
+    const bool live = in && tt >= 0 && tt < C.T1 - 1;
     count_invalid(n_invalid, in && !live, hl);
     const int64_t trow = live ? tt : 0;
     const float *p0 = C.price + (size_t)trow * n;

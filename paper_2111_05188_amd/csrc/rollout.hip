@@ -258,7 +258,7 @@ __global__ __launch_bounds__(NWM *WAVE) void rollout_kernel(RolloutArgs A)
     if (mine) {
         const int e = ebase + sl;
         const int64_t tt = A.t[e];
-        live = tt >= 0 && tt + A.L <= C.T1 - 1;
+        live = tt >= 0 && tt <= C.T1 - 1 - A.L;
         if (A.n_invalid && !live && hl == 0) atomicAdd(A.n_invalid, 1);
         // state (also for envs that are not stepped: their taps repeat it)
         for (int i = hl; i < n; i += HALF) OS[sl * n + i] = A.shares[(size_t)e * n + i];

@@ -441,7 +441,7 @@ __device__ __forceinline__ Slot env_slot(const RolloutArgs &A, int agent, int eb
     s.e = ebase + s.sl;
     s.agent = agent;
     s.t0 = s.mine ? A.t[s.e] : -1;
-    s.live = s.t0 >= 0 && s.t0 + A.L <= A.env.T1 - 1;
+    s.live = s.t0 >= 0 && s.t0 <= A.env.T1 - 1 - A.L;
     return s;
 }
 

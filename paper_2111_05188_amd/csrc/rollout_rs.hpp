@@ -482,7 +482,7 @@ __device__ __forceinline__ void env_role(const RolloutArgs &A, const Lds &s, con
     }
     if (mine) {
         t0 = A.t[e];
-        live = t0 >= 0 && t0 + A.L <= C.T1 - 1;
+        live = t0 >= 0 && t0 <= C.T1 - 1 - A.L;
         if (A.n_invalid && !live && sl16 == 0) atomicAdd(A.n_invalid, 1);
         st.cash = A.cash[e];
 #pragma unroll

@@ -95,6 +95,23 @@ def test_env_step_out_of_range_env_is_noop():
     assert st.n_invalid.item() == 2        # the two envs that were not stepped
 
 
+def test_env_step_time_index_at_the_end_of_its_range():
+    """t + 1 past the largest int64 is out of the market too (the sum must not
+    wrap)."""
+    say("[env_step] time indices at the end of their range")
+    cfg = W.get_config("tiny")
+    mk = W.make_market(cfg)
+    mkt = tp.MarketT(torch.from_numpy(mk.price).cuda(), torch.from_numpy(mk.ind).cuda())
+    st = tp.StateT.empty(3, cfg.n, count_invalid=True)
+    far = [2 ** 63 - 1, 2 ** 63 - 2]
+    st.t.copy_(torch.tensor([*far, 10]))
+    rew = torch.empty(3, device="cuda")
+    tp.env_step(mkt, problem.env_cfg(cfg), st, torch.full((3, cfg.n), 0.5, device="cuda"), rew)
+    torch.cuda.synchronize()
+    assert torch.isnan(rew[:2]).all() and torch.isfinite(rew[2])
+    assert st.t.cpu().tolist() == [*far, 11] and st.n_invalid.item() == 2
+
+
 @pytest.mark.parametrize("name", ["tiny", "nasdaq100"])
 def test_env_reset(name):
     say(f"[env_reset] {name}")

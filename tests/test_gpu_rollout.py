@@ -399,6 +399,29 @@ def test_env_without_room_other_kernels(n, I, hidden, dtype, E, kernel):
     compare_rollout(cfg, pb, out, ids, 20)
 
 
+@pytest.mark.parametrize("name,n,I,hidden,dtype,kernel", [
+    ("nasdaq100", 100, 8, (256, 256), "bf16", 1), ("tiny", 5, 4, (1028, 64), "f32", GENERIC),
+    ("tiny", 5, 4, (512, 128), "bf16", GENERIC), ("tiny", 5, 4, (64, 64), "f32", FOUR),
+    ("tiny", 33, 3, (256, 128), "bf16", FOUR),
+])
+def test_time_index_at_the_end_of_its_range(name, n, I, hidden, dtype, kernel):
+    """t + L past the largest int64 is no room either (the sum must not wrap)."""
+    cfg = W.get_config(name).with_(name="last", n=n, n_ind=I, hidden=hidden, dtype=dtype, N=780,
+                                   E=9, L=20)
+    pb, _ = build_problem(cfg, W.make_market(cfg), np.zeros(9, np.int64))
+    assert tp.rollout_kernel(pb.mkt, pb.actor) == kernel
+    pb.state = tp.StateT.empty(9, n, count_invalid=True)
+    pb.reset()
+    far = [2 ** 63 - 1, 2 ** 63 - 20]
+    pb.state.t[2], pb.state.t[7] = far
+    say(f"[rollout] time indices past the market, {n} stocks {hidden} {dtype}")
+    pb.rollout(SEED, 0, 20)
+    torch.cuda.synchronize()
+    assert pb.state.n_invalid.item() == 2 and pb.state.t[[2, 7]].tolist() == far
+    assert torch.isnan(pb.traj.reward[:20, [2, 7]]).all()
+    assert torch.isfinite(pb.traj.reward[:20, [0, 1, 3, 4, 5, 6, 8]]).all()
+
+
 def test_rollout_errors():
     cfg = W.get_config("tiny")
     mk = W.make_market(cfg)
